@@ -2,22 +2,32 @@
 // token is the target's most likely one; ties go to the lowest index).
 //
 // bf16 path: the product is W[V][H] x X[N][H]^T, a skinny GEMM that streams
-// W from HBM once; it is bound by HBM bandwidth, so the design is about
-// keeping enough whole cache lines in flight:
-//  * A persistent grid (one block per CU) walks 128-row vocabulary tiles
-//    round-robin; the K dimension is cut into 64-element chunks.  The last,
-//    partial round of tiles is dealt out in 32-row groups (one per compute
-//    wave), so that no block streams more than one group beyond the average
-//    (1187 tiles on 256 blocks: 4 tiles + 2 or 3 groups each, instead of 4
-//    or 5 tiles).
-//  * The streaming core (stream_core.h): two loader waves copy each W
-//    chunk (128 rows x 128 B) and a third the X chunk (all nodes x 128 B)
-//    straight into an LDS ring with global_load_lds; four compute waves own
-//    32 rows each and run the MFMAs from LDS, never issuing global loads in
-//    the loop.
-//  * Each lane ends a tile with 16 logits of one node; the per-node argmax is
-//    kept in registers across tiles, merged across the block's waves in LDS
-//    and across blocks by a small finalize kernel (value, then lowest index).
+// W from HBM once.  Up to 64 nodes HBM binds it; from 128 on the power cap
+// does: the matrix cores' work and every byte moved into LDS lower the clock
+// (2.4 GHz at 32 nodes, 1.6-1.7 at 128 and 256; with zero hidden rows the
+// same kernel runs 128 nodes at 2.3 GHz and at the HBM rate).  So the design
+// keeps whole lines in flight and moves few X bytes per W byte:
+//  * A persistent grid, one block per CU.  The vocabulary's 32-row groups
+//    are dealt out evenly and in order, so no block streams more than one
+//    group beyond the average, and a block cuts its groups into tiles of
+//    nearly equal size (18 or 19 groups: three tiles of 6 or 7).
+//  * Tiles of up to 8 groups (256 rows; 4 at 129-256 nodes, where the
+//    accumulators of two groups a wave do not fit): every tile re-reads all
+//    of X from L2, so taller tiles move half the X bytes of 128-row ones.
+//    Per call, 128-row tiles against this: 303.0 -> 270.2 us at 128 nodes,
+//    H 5120, V 152064; 321.6 -> 297.7 at 256 nodes, H 4096, V 128256 (the
+//    fragment reads a k-step ahead, below); 185.7 -> 185.0 at 64 nodes,
+//    H 4096, V 151936 (HBM-bound at 6.7 TB/s).
+//  * The streaming core (stream_core.h): four loader waves copy each W
+//    chunk (a group's 32 rows x 128 B per slot) and the X chunk (all nodes x
+//    128 B) straight into an LDS ring with global_load_lds; four compute
+//    waves own up to two groups each and run the MFMAs from LDS, never
+//    issuing global loads in the loop, with the fragments of the next k-step
+//    read under the MFMAs of this one.
+//  * Each lane ends a tile with 16 logits per group of one node; the per-node
+//    argmax is kept in registers across tiles, merged across the block's
+//    waves in LDS and across blocks by a small finalize kernel (value, then
+//    lowest index).
 #include <math.h>
 
 #include "device_common.h"
@@ -34,83 +44,44 @@ struct Cand {
 
 constexpr int kLmRows = kStreamRows;  // vocabulary rows per tile (4 waves x 32)
 
-template <int NB, bool PACKED>
-__global__ __launch_bounds__(kStreamThreads) void lmhead_bf16_kernel(const uint16_t* __restrict__ X,
-                                                          const uint16_t* __restrict__ Wt, int N, int H, int V,
-                                                          Cand* __restrict__ partial, float* __restrict__ logits) {
-  using R = StreamRing<NB>;
-  static_assert(R::BYTES + 4 * 32 * NB * sizeof(Cand) <= 160 * 1024, "LDS capacity");
+// First of the n items that part t of T gets when they are dealt out evenly
+// in order (the first n % T parts hold one more).
+__device__ __forceinline__ int even_cut(int n, int t, int T) { return n / T * t + min(t, n % T); }
+
+template <int NB, int RG, bool PACKED>
+__global__ __launch_bounds__(kTallThreads) void lmhead_bf16_kernel(const uint16_t* __restrict__ X,
+                                                                   const uint16_t* __restrict__ Wt, int N, int H,
+                                                                   int V, Cand* __restrict__ partial,
+                                                                   float* __restrict__ logits) {
+  using R = TallRing<NB, RG>;
+  static_assert(4 * 32 * NB * sizeof(Cand) <= R::BYTES, "the reduction reuses the ring");
   __shared__ __attribute__((aligned(1024))) uint8_t lds[R::BYTES];
-  __shared__ Cand red[4][32 * NB];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int chunks = H / 64;
   const int b = (int)blockIdx.x, grid = (int)gridDim.x;
-  const int ntiles_all = (V + kLmRows - 1) / kLmRows;
-  const int full_rounds = ntiles_all / grid;                  // rounds of whole tiles for every block
-  const int rem_groups = (ntiles_all - full_rounds * grid) * 4;  // 32-row groups of the last round
-  const int my_tiles = full_rounds + (rem_groups > b ? 1 : 0);
-  const int total = my_tiles * chunks;  // chunks this block streams
-  // 32-row group of slot s (compute wave s) in the block's tile t, or -1
-  auto group_of = [&](int t, int s) {
-    if (t < full_rounds) return 4 * (b + t * grid) + s;
-    const int rg = b + s * grid;
-    return rg < rem_groups ? 4 * full_rounds * grid + rg : -1;
-  };
+  const int groups = (V + 31) / 32;
+  const int g_lo = even_cut(groups, b, grid);
+  const int n_my = even_cut(groups, b + 1, grid) - g_lo;  // >= 1: grid <= groups
+  const int T = (n_my + R::SLOTS - 1) / R::SLOTS;
+  const int per = n_my / T, more = n_my % T;
+  const auto cut = [&](int t) { return g_lo + per * t + min(t, more); };  // first group of tile t
 
   if (wave >= 4) {
-    // -------------------------------------- loaders: W slots 0-1 (4), 2-3 (5), X (6)
-    const bool is_x = wave == 6;
-    const int s_lo = 2 * (wave - 4);  // first W slot of this loader
-    // Per-slot source of the tile whose chunks are being issued, set once
-    // per tile: the group's first chunk and the element step per chunk.  An
-    // empty slot (last round only) copies a line of X instead (step 0),
-    // which sits in L2, so that every chunk is the same number of DMA
-    // instructions.
-    int issue_tile = -1;
-    const uint16_t* sbase[4];
-    int sstep[4];
-    auto set_tile = [&](int t) {
-#pragma unroll
-      for (int s4 = 0; s4 < 4; ++s4) {
-        const int gi = group_of(t, s4);
-        if (gi < 0) {
-          sbase[s4] = X + (size_t)(b % N) * H + min(lane * 8, H - 8);
-          sstep[s4] = 0;
-        } else if (PACKED) {
-          // the group's chunk is a contiguous 4 KiB run of the tile's 16 KiB
-          // block, already swizzled
-          sbase[s4] = Wt + ((size_t)(gi / 4) * chunks * kLmRows + 32 * (gi % 4)) * 64 + lane * 8;
-          sstep[s4] = kLmRows * 64;
-        } else {
-          sbase[s4] = Wt + (size_t)32 * gi * H;  // group row 0; rows and pieces per lane below
-          sstep[s4] = 64;
-        }
-      }
-      issue_tile = t;
-    };
-    auto issue = [&](int q, int stage) {
-      const int t = q / chunks;
-      const int kc = q % chunks;
-      if (!is_x) {
-        uint8_t* dst = lds + stage * R::WS;
-        if (t != issue_tile) set_tile(t);
-        // slot s4's 32 rows go to LDS rows 32 s4 .. 32 s4 + 31 of the stage
-#pragma unroll
-        for (int s4 = 0; s4 < 4; ++s4) {
-          if (s4 / 2 != s_lo / 2) continue;
-          if (PACKED || sstep[s4] == 0) {
-            dma_w_slot_packed(sbase[s4] + kc * sstep[s4], sstep[s4], dst + s4 * 4096);
-          } else {
-            dma_w_slot_rows(Wt, H, 32 * group_of(t, s4), V, kc, dst + s4 * 4096, lane);
-          }
-        }
-      } else {
-        dma_x_chunk<NB>(X, N, H, kc, lds + R::XREG + stage * R::XS, lane);
-      }
-    };
-    if (is_x) loader_stream<R::NS, R::XDMA>(total, issue);
-    else loader_stream<R::NS, R::WDMA>(total, issue);
-    __syncthreads();  // matches the compute waves' final reduction barrier
+    const int ld = wave - 4;
+    XShare<NB> xs(X, N, H, ld, lane);
+    for_tiles_load<NB, RG>(T, chunks, ld, cut,
+                           [&](int g, int kc, uint8_t* dst) {
+                             if (PACKED)
+                               dma_w_slot_packed(Wt + ((size_t)(g / 4) * chunks + kc) * (kStreamRows * 64) +
+                                                     32 * 64 * (g % 4) + lane * 8,
+                                                 1, dst);
+                             else
+                               dma_w_slot_rows(Wt, H, 32 * g, V, kc, dst, lane);
+                           },
+                           xs, lds);
+    __syncthreads();  // matches the compute waves' barriers around the final reduction
+    __syncthreads();
     return;
   }
 
@@ -118,8 +89,6 @@ __global__ __launch_bounds__(kStreamThreads) void lmhead_bf16_kernel(const uint1
   const int c = lane & 31, u = lane >> 5;
   uint32_t off[4];
   frag_offsets(lane, off);
-  const uint32_t wrow = wave * 32 * 128;
-
   float bestv[NB];
   int besti[NB];
 #pragma unroll
@@ -127,33 +96,31 @@ __global__ __launch_bounds__(kStreamThreads) void lmhead_bf16_kernel(const uint1
     bestv[nb] = -INFINITY;
     besti[nb] = 0x7FFFFFFF;
   }
-  f32x16 acc[NB];
-  int gi = -1;  // this wave's 32-row group in the current tile
-  for (int q = 0; q < total; ++q) {
-    const int kc = q % chunks;
-    if (kc == 0) {
-      gi = group_of(q / chunks, wave);
+  int stage = 0;
+  wg_barrier();  // the first chunk has landed
+  for (int t = 0; t < T; ++t) {
+    const int g0 = cut(t), ng = cut(t + 1) - g0;
+    f32x16 acc[RG][NB];
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) acc[nb] = f32x16{};
-    }
-    const int stage = q % R::NS;
-    wg_barrier();
-    if (gi < 0) continue;  // empty slot of the last round (barriers only)
-    chunk_mfma<NB>(lds + stage * R::WS + wrow, lds + R::XREG + stage * R::XS, off, acc);
-
-    if (kc == chunks - 1) {
-      // tile done: acc[nb][j] = logit of vocabulary row v0 + 8(j/4) + 4u + j%4, node 32nb + c
-      const int v0 = 32 * gi;
+    for (int r = 0; r < RG; ++r)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) acc[r][nb] = f32x16{};
+    tall_tile<NB, RG>(chunks, t + 1 == T, ng, wave, lds, off, stage, acc);
+    // acc[r][nb][j] = logit of vocabulary row 32 g + 8(j/4) + 4u + j%4, g = g0 + wave + 4r, node 32nb + c
+#pragma unroll
+    for (int r = 0; r < RG; ++r) {
+      if (wave + 4 * r >= ng) break;
+      const int v0 = 32 * (g0 + wave + 4 * r);
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
         float bv = -INFINITY;
         int bi = 0x7FFFFFFF;
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
-          const int r = v0 + 8 * (j / 4) + 4 * u + (j % 4);
-          if (r < V && acc[nb][j] > bv) {
-            bv = acc[nb][j];
-            bi = r;
+          const int row = v0 + 8 * (j / 4) + 4 * u + (j % 4);
+          if (row < V && acc[r][nb][j] > bv) {
+            bv = acc[r][nb][j];
+            bi = row;
           }
         }
         const float ov = shfl_xor_f(bv, 32);
@@ -171,22 +138,26 @@ __global__ __launch_bounds__(kStreamThreads) void lmhead_bf16_kernel(const uint1
           if (n < N)
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
-              const int r = v0 + 8 * (j / 4) + 4 * u + (j % 4);
-              if (r < V) logits[(size_t)n * V + r] = acc[nb][j];
+              const int row = v0 + 8 * (j / 4) + 4 * u + (j % 4);
+              if (row < V) logits[(size_t)n * V + row] = acc[r][nb][j];
             }
         }
       }
     }
   }
+  Cand* red = reinterpret_cast<Cand*>(lds);
+  __syncthreads();  // every wave is past its last read of the ring
   if (u == 0)
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) red[wave][32 * nb + c] = Cand{bestv[nb], besti[nb]};
+    for (int nb = 0; nb < NB; ++nb) red[wave * 32 * NB + 32 * nb + c] = Cand{bestv[nb], besti[nb]};
   __syncthreads();
   for (int n = threadIdx.x; n < N; n += 256) {
-    Cand b = red[0][n];
-    for (int w2 = 1; w2 < 4; ++w2)
-      if (better(red[w2][n].v, red[w2][n].i, b.v, b.i)) b = red[w2][n];
-    partial[(size_t)blockIdx.x * N + n] = b;
+    Cand best = red[n];
+    for (int w2 = 1; w2 < 4; ++w2) {
+      const Cand o = red[w2 * 32 * NB + n];
+      if (better(o.v, o.i, best.v, best.i)) best = o;
+    }
+    partial[(size_t)blockIdx.x * N + n] = best;
   }
 }
 
@@ -273,8 +244,8 @@ LmPlan lm_plan(int N, int H, int V, ooo_dtype dt) {
   LmPlan p{};
   if (dt == OOO_BF16) {
     p.nb = N <= 32 ? 1 : N <= 64 ? 2 : N <= 128 ? 4 : 8;
-    const int tiles = (V + kLmRows - 1) / kLmRows;
-    p.blocks = tiles < device_cus() ? tiles : device_cus();  // persistent grid: one block per CU
+    const int groups = (V + 31) / 32;
+    p.blocks = groups < device_cus() ? groups : device_cus();  // persistent grid: one block per CU
   } else {
     p.blocks = (V + 255) / 256;
   }
@@ -342,17 +313,17 @@ extern "C" int ooo_lmhead_argmax(const void* hidden, const void* weight, int32_t
     const uint16_t* X = (const uint16_t*)hidden;
     const uint16_t* W = (const uint16_t*)weight;
     const bool pk = weight_layout == OOO_W_PACKED;
-#define OOO_LM_LAUNCH(NBV)                                                                                   \
-  do {                                                                                                      \
-    if (pk)                                                                                                 \
-      lmhead_bf16_kernel<NBV, true><<<p.blocks, kStreamThreads, 0, st>>>(X, W, n_nodes, hidden_dim, vocab, part, logits); \
-    else                                                                                                    \
-      lmhead_bf16_kernel<NBV, false><<<p.blocks, kStreamThreads, 0, st>>>(X, W, n_nodes, hidden_dim, vocab, part, logits); \
+#define OOO_LM_LAUNCH(NBV, RGV)                                                                                        \
+  do {                                                                                                                \
+    if (pk)                                                                                                           \
+      lmhead_bf16_kernel<NBV, RGV, true><<<p.blocks, kTallThreads, 0, st>>>(X, W, n_nodes, hidden_dim, vocab, part, logits); \
+    else                                                                                                              \
+      lmhead_bf16_kernel<NBV, RGV, false><<<p.blocks, kTallThreads, 0, st>>>(X, W, n_nodes, hidden_dim, vocab, part, logits); \
   } while (0)
-    if (p.nb == 1) OOO_LM_LAUNCH(1);
-    else if (p.nb == 2) OOO_LM_LAUNCH(2);
-    else if (p.nb == 4) OOO_LM_LAUNCH(4);
-    else OOO_LM_LAUNCH(8);
+    if (p.nb == 1) OOO_LM_LAUNCH(1, 2);
+    else if (p.nb == 2) OOO_LM_LAUNCH(2, 2);
+    else if (p.nb == 4) OOO_LM_LAUNCH(4, 2);
+    else OOO_LM_LAUNCH(8, 1);
 #undef OOO_LM_LAUNCH
   } else {
     lmhead_f32_kernel<<<dim3(p.blocks, n_nodes), 256, 0, st>>>((const float*)hidden, (const float*)weight, n_nodes,

@@ -314,6 +314,19 @@ def _run_lm(x, w, dt, want_logits=True, packed=False):
     return ids.cpu().numpy(), mx.cpu().numpy(), (lg.cpu().numpy() if want_logits else None)
 
 
+# tall tiles: tiles shorter than the LDS ring (one or two chunks) with several
+# tiles a block whose slot counts differ, a group count just above and below
+# the grid, a last group with one row, and one row of vocabulary
+LM_CASES += [
+    (64, 64, 200001, "bf16"),
+    (5, 128, 140000, "bf16"),
+    (100, 64, 130000, "bf16"),
+    (40, 320, 8193, "bf16"),
+    (17, 256, 8191, "bf16"),
+    (3, 64, 1, "bf16"),
+]
+
+
 LM_RUNS = [(c, False) for c in LM_CASES] + [(c, True) for c in LM_CASES if c[3] == "bf16"]
 
 
