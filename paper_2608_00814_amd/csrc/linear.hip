@@ -8,25 +8,35 @@
 //  * W is packed once into 16 KiB blocks of 128 rows x 64 columns (the LM
 //    head's layout, ooo_linear_pack); the work is the sequence of (128-row
 //    tile, 64-column chunk) blocks in tile-major order.
-//  * Stream-K: a persistent grid (one block per CU) where block b takes the
-//    contiguous run of chunks [C b / B, C (b + 1) / B).  Every block streams
-//    the same number of bytes whatever O and K are; a run covers the end of
+//  * Stream-K: a persistent grid (one block per CU) where block b takes a
+//    contiguous run of chunks, C / B of them or one more.  Every block
+//    streams the same bytes whatever O and K are; a run covers the end of
 //    one tile and the start of the next.
-//  * Inside a block, the LM head's streaming core (stream_core.h): two
-//    loader waves DMA the W chunk (two 32-row slots each) and a third the X
-//    chunk into an LDS ring; four compute waves run mfma_f32_32x32x16_bf16
-//    (32 W rows x the nodes each).
-//  * At the end of each tile segment a block stores its partial sums in the
-//    workspace as fp16 ([node][128 rows]) times a power of two per compute
-//    wave (its 32 rows), chosen so that the wave's largest magnitude lies
-//    in [2^14, 2^15): half the bytes of fp32, with the range of fp32.  A
-//    reduce kernel adds a tile's partials in float32 in block order
-//    (deterministic, no atomics) and applies the epilogue: store fp32 or
-//    bf16, add into an fp32 output (the residual rows), or silu(gate) * up
-//    of a fused gate/up projection.
+//  * Inside a block, the LM head's streaming core (stream_core.h) with
+//    128-row tiles: four loader waves copy one 32-row W slot each and a
+//    quarter of the X rows there are into an LDS ring; four compute waves
+//    run mfma_f32_32x32x16_bf16 (32 W rows x the nodes each).  Taller tiles
+//    move fewer X bytes but twice the partial sums: 256-row tiles measured
+//    214.6 against 202.4 us for two Qwen3-8B layers at one node, 262.6
+//    against 238.2 at 64.
+//  * At the end of each tile segment a block stores its partial sums (of the
+//    nodes there are) in the workspace as fp16 ([node][128 rows]) times a
+//    power of two per compute wave (its 32 rows), chosen so that the wave's
+//    largest magnitude lies in [2^14, 2^15): half the bytes of fp32, with
+//    the range of fp32.  A reduce kernel adds a tile's partials in float32
+//    in block order (deterministic, no atomics) and applies the epilogue:
+//    store fp32 or bf16, add into an fp32 output (the residual rows), or
+//    silu(gate) * up of a fused gate/up projection.  Where the partials lie
+//    follows from two 32-bit divisions per tile in registers (a list built
+//    in LDS by one thread per tile cost each of these kernels about 1.5 us).
+//  * The gate/up projection usually has enough rows for every block to own
+//    whole output columns: then it runs without partial sums
+//    (linear_swiglu_kernel).
+// Two layers at the Qwen3-8B shape (graph replay), with 128-row tiles of
+// seven waves, padded X and partial rows, slot lists in LDS and SwiGLU
+// through stream-K against this: 242.6 -> 202.5 us at one node, 281.1 ->
+// 238.2 at 64; one layer at H 5120, I 27648, 128 nodes 317.2 -> 275.3.
 #include <math.h>
-
-#include <vector>
 
 #include "device_common.h"
 #include "ooo_internal.h"
@@ -36,8 +46,6 @@
 namespace ooo {
 namespace {
 
-constexpr int kRows = kStreamRows;  // W rows per tile (4 compute waves x 32)
-
 // Stream-K partial sums in the workspace: slot k (block b, segment j: k =
 // b * seg + j) holds v[k][node][128 rows] in fp16 and sc[k][4], the factor
 // that turns the fp16 values of rows 32 w .. 32 w + 31 back into the sums.
@@ -46,54 +54,40 @@ struct Partials {
   float* sc;
 };
 
-// first chunk of block b's run
-__host__ __device__ __forceinline__ long long run_lo(long long C, int b, int B) { return C * b / B; }
+// The stream-K cut: C chunks (tile-major) in B runs, q = C / B, r = C % B:
+// the first r runs hold one chunk more.
+struct Runs {
+  int q, r, B, seg;
+  __host__ __device__ __forceinline__ int lo(int b) const { return q * b + (b < r ? b : r); }
+  // the run that holds chunk x
+  __host__ __device__ __forceinline__ int of(int x) const {
+    const int head = r * (q + 1);
+    return x < head ? (int)((unsigned)x / (unsigned)(q + 1)) : r + (int)((unsigned)(x - head) / (unsigned)q);
+  }
+};
 
 template <int NB, bool PACKED>
-__global__ __launch_bounds__(kStreamThreads) void linear_bf16_kernel(const uint16_t* __restrict__ X,
-                                                          const uint16_t* __restrict__ Wt, int N, int K, int O,
-                                                          int seg_per_block, Partials part) {
-  using R = StreamRing<NB>;
+__global__ __launch_bounds__(kTallThreads) void linear_bf16_kernel(const uint16_t* __restrict__ X,
+                                                                   const uint16_t* __restrict__ Wt, int N, int K,
+                                                                   int O, Runs runs, Partials part) {
   constexpr int NPAD = 32 * NB;
-  __shared__ __attribute__((aligned(1024))) uint8_t lds[R::BYTES];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[kRingBytes];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int KC = K / 64;
-  const int tiles = (O + kRows - 1) / kRows;
-  const long long C = (long long)tiles * KC;
-  const int b = (int)blockIdx.x, B = (int)gridDim.x;
-  const long long lo = run_lo(C, b, B);
-  const int total = (int)(run_lo(C, b + 1, B) - lo);  // chunks of this block (>= 1: B <= C)
-  const int first_tile = (int)(lo / KC);
+  const int groups = (O + 31) / 32;
+  const int b = (int)blockIdx.x;
+  const int lo = runs.lo(b);
+  const int total = runs.lo(b + 1) - lo;  // chunks of this block (>= 1: B <= C)
+  const int first_tile = (int)((unsigned)lo / (unsigned)KC), kc0 = lo - first_tile * KC;
+  const auto tile = [&](int t) { return GroupRange{4 * t, min(4 * t + 4, groups)}; };
+  const Ring ring(min(4, groups), N, NB);
 
   if (wave >= 4) {
-    // ------------------------------------------ loaders: W rows 0-63 (4), 64-127 (5), X (6)
-    const bool is_x = wave == 6;
-    const int half = wave - 4;
-    // (tile, chunk) of the next chunk to issue; issues come in order
-    int it = first_tile, ikc = (int)(lo - (long long)first_tile * KC);
-    auto issue = [&](int q, int stage) {
-      const int t = it, kc = ikc;
-      if (++ikc == KC) {
-        ikc = 0;
-        ++it;
-      }
-      if (!is_x) {
-        // this loader's slots 2 half, 2 half + 1: tile rows 64 half .. +63
-        uint8_t* dst = lds + stage * R::WS + half * (R::WS / 2);
-#pragma unroll
-        for (int sl = 0; sl < 2; ++sl) {
-          const int s4 = 2 * half + sl;
-          if (PACKED)
-            dma_w_slot_packed(Wt + (((size_t)t * KC + kc) * kRows + 32 * s4) * 64 + lane * 8, 1, dst + sl * 4096);
-          else
-            dma_w_slot_rows(Wt, K, t * kRows + 32 * s4, O, kc, dst + sl * 4096, lane);
-        }
-      } else {
-        dma_x_chunk<NB>(X, N, K, kc, lds + R::XREG + stage * R::XS, lane);
-      }
-    };
-    if (is_x) loader_stream<R::NS, R::XDMA>(total, issue);
-    else loader_stream<R::NS, R::WDMA>(total, issue);
+    const int ld = wave - 4;
+    XShare<NB> xs(X, N, K, ld, lane);
+    GroupSlots<1, PACKED> slots(Wt, KC, O, K, lane);
+    tall_load<NB, 1>(first_tile, kc0, total, KC, (groups - 1) % 4 + 1, ld, tile, slots, xs, ring, lds);
     return;
   }
 
@@ -101,160 +95,230 @@ __global__ __launch_bounds__(kStreamThreads) void linear_bf16_kernel(const uint1
   const int c = lane & 31, u = lane >> 5;
   uint32_t off[4];
   frag_offsets(lane, off);
-  const uint32_t wrow = wave * 32 * 128;
-  f32x16 acc[NB];
-  int t = first_tile, kc = (int)(lo - (long long)first_tile * KC) - 1;
-  for (int q = 0; q < total; ++q) {
-    if (++kc == KC) {
-      kc = 0;
-      ++t;
+  int stage = 0, left = total, kc = kc0;
+  wg_barrier();  // the first chunk has landed
+  for (int t = first_tile; left > 0; ++t) {
+    const int n = min(left, KC - kc), ng = tile(t).hi - tile(t).lo;
+    left -= n;
+    kc = 0;
+    f32x16 acc[1][NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) acc[0][nb] = f32x16{};
+    tall_tile<NB, 1>(n, left == 0, ng, wave, lds, ring, off, stage, acc);
+    if (wave >= ng) continue;
+    // segment done: acc[0][nb][j] = partial of tile row 32 wave + 8(j/4) + 4u + j%4, node 32nb + c.
+    // Scale: the wave's largest finite magnitude a < 2^ex (over the nodes
+    // there are) goes to [2^14, 2^15) (fp16 holds up to 65504); exact powers
+    // of two both ways.  Inf and NaN stay what they are and do not set it.
+    const size_t slot = (size_t)b * runs.seg + (t - first_tile);
+    float amax = 0.f;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      const bool in = 32 * nb + c < N;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const float m = __builtin_fabsf(acc[0][nb][j]);
+        amax = __builtin_fmaxf(amax, in && m < INFINITY ? m : 0.f);
+      }
     }
-    if (q == 0 || kc == 0) {
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) acc[nb] = f32x16{};
-    }
-    const int stage = q % R::NS;
-    wg_barrier();
-    chunk_mfma<NB>(lds + stage * R::WS + wrow, lds + R::XREG + stage * R::XS, off, acc);
-    if (q == total - 1 || kc == KC - 1) {
-      // segment done: acc[nb][j] = partial of tile row wave*32 + 8(j/4) + 4u + j%4, node 32nb + c.
-      // Scale: the wave's largest finite magnitude a < 2^ex goes to
-      // [2^14, 2^15) (fp16 holds up to 65504); exact powers of two both
-      // ways.  Inf and NaN stay what they are and do not set the scale.
-      float amax = 0.f;
+    for (int o = 32; o > 0; o >>= 1) amax = __builtin_fmaxf(amax, shfl_xor_f(amax, o));
+    const int ex = min(max(__builtin_amdgcn_frexp_expf(amax), -100), 100);
+    const float mul = __builtin_amdgcn_ldexpf(1.f, 15 - ex);
+    uint16_t* dst = part.v + slot * NPAD * kStreamRows + 32 * wave;
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          const float m = __builtin_fabsf(acc[nb][j]);
-          amax = __builtin_fmaxf(amax, m < INFINITY ? m : 0.f);
-        }
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) amax = __builtin_fmaxf(amax, shfl_xor_f(amax, o));
-      const int ex = min(max(__builtin_amdgcn_frexp_expf(amax), -100), 100);
-      const float mul = __builtin_amdgcn_ldexpf(1.f, 15 - ex);
-      const size_t slot = (size_t)b * seg_per_block + (t - first_tile);
-      uint16_t* dst = part.v + slot * NPAD * kRows;
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
+    for (int nb = 0; nb < NB; ++nb)
+      if (32 * nb + c < N)
 #pragma unroll
         for (int jq = 0; jq < 4; ++jq)
-          *reinterpret_cast<u32x2*>(dst + (size_t)(32 * nb + c) * kRows + wave * 32 + 8 * jq + 4 * u) =
-              u32x2{pack_f16x2(acc[nb][4 * jq] * mul, acc[nb][4 * jq + 1] * mul),
-                    pack_f16x2(acc[nb][4 * jq + 2] * mul, acc[nb][4 * jq + 3] * mul)};
-      if (lane == 0) part.sc[slot * 4 + wave] = __builtin_amdgcn_ldexpf(1.f, ex - 15);
+          *reinterpret_cast<u32x2*>(dst + (size_t)(32 * nb + c) * kStreamRows + 8 * jq + 4 * u) =
+              u32x2{pack_f16x2(acc[0][nb][4 * jq] * mul, acc[0][nb][4 * jq + 1] * mul),
+                    pack_f16x2(acc[0][nb][4 * jq + 2] * mul, acc[0][nb][4 * jq + 3] * mul)};
+    if (lane == 0) part.sc[slot * 4 + wave] = __builtin_amdgcn_ldexpf(1.f, ex - 15);
+  }
+}
+
+// W sources of the kernel below: unit g's 16 gate rows, then its 16 up rows
+// (row 16 + r of the slot swizzles as row r).
+template <int RG, bool PACKED>
+struct PairSlots {
+  const uint16_t* W;
+  int KC, K, inter, lane;
+  const uint16_t* p[RG][2];
+  __device__ __forceinline__ PairSlots(const uint16_t* w, int kc, int k, int i, int ln)
+      : W(w), KC(kc), K(k), inter(i), lane(ln) {}
+  __device__ __forceinline__ void set(int r, int g, int kc) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int row0 = 16 * g + h * inter;
+      p[r][h] = PACKED ? W + ((size_t)(row0 / 128) * KC + kc) * (kStreamRows * 64) + (row0 % 128) * 64
+                       : W + (size_t)row0 * K + kc * 64;
+    }
+  }
+  __device__ __forceinline__ void dma(int r, uint8_t* dst) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int jj = 0; jj < 2; ++jj) {
+        const int row = 8 * jj + lane / 8;
+        const uint16_t* src = PACKED ? p[r][h] + jj * 512 + lane * 8
+                                     : p[r][h] + (size_t)row * K + ((lane % 8) ^ piece_swz(row)) * 8;
+        __builtin_amdgcn_global_load_lds(OOO_GLB(src), OOO_LDS(dst + h * 2048 + jj * 1024), 16, 0, kStreamOnce);
+      }
+      p[r][h] += PACKED ? kStreamRows * 64 : 64;
+    }
+  }
+};
+
+// silu(gate) * up without partial sums: a block owns whole output columns.
+// A unit is 16 gate rows and the 16 up rows of the same columns; they share
+// a 32-row slot (gate rows in its first half), so a lane's accumulators j
+// and j + 8 are the gate and the up value of one output.  The units are
+// dealt out evenly over the blocks, each block streams the whole K of its
+// units, and the activation is applied to the float32 sums in registers:
+// no workspace traffic, no second kernel, no fp16 rounding.
+template <int NB, int RG, bool PACKED>
+__global__ __launch_bounds__(kTallThreads) void linear_swiglu_kernel(const uint16_t* __restrict__ X,
+                                                                     const uint16_t* __restrict__ Wt, int N, int K,
+                                                                     int inter, uint16_t* __restrict__ out) {
+  constexpr int SLOTS = 4 * RG;
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[kRingBytes];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int KC = K / 64;
+  const int units = inter / 16, grid = (int)gridDim.x, b = (int)blockIdx.x;  // grid <= units
+  const int T = (units + SLOTS * grid - 1) / (SLOTS * grid);
+  const int per = units / (T * grid), more = units % (T * grid);
+  const auto first = [&](int i) { return per * i + min(i, more); };  // first unit of tile i of T * grid
+  const auto tile = [&](int t) { return GroupRange{first(b + t * grid), first(b + t * grid + 1)}; };
+  const Ring ring(per + (more > 0), N, NB);
+
+  if (wave >= 4) {
+    const int ld = wave - 4;
+    XShare<NB> xs(X, N, K, ld, lane);
+    PairSlots<RG, PACKED> slots(Wt, KC, K, inter, lane);
+    tall_load<NB, RG>(0, 0, T * KC, KC, per, ld, tile, slots, xs, ring, lds);
+    return;
+  }
+
+  const int c = lane & 31, u = lane >> 5;
+  uint32_t off[4];
+  frag_offsets(lane, off);
+  int stage = 0;
+  wg_barrier();  // the first chunk has landed
+  for (int t = 0; t < T; ++t) {
+    const int u0 = tile(t).lo, ng = tile(t).hi - u0;
+    f32x16 acc[RG][NB];
+#pragma unroll
+    for (int r = 0; r < RG; ++r)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) acc[r][nb] = f32x16{};
+    tall_tile<NB, RG>(KC, t + 1 == T, ng, wave, lds, ring, off, stage, acc);
+    // acc[r][nb][j], j < 8: gate of column 16 unit + 8(j/4) + 4u + j%4, node 32nb + c; [j + 8]: its up value
+#pragma unroll
+    for (int r = 0; r < RG; ++r) {
+      if (wave + 4 * r >= ng) break;
+      uint16_t* o = out + 16 * (u0 + wave + 4 * r) + 4 * u;
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const int n = 32 * nb + c;
+        if (n >= N) continue;
+#pragma unroll
+        for (int jq = 0; jq < 2; ++jq) {
+          float y[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float gt = acc[r][nb][4 * jq + e];
+            y[e] = gt / (1.f + expf(-gt)) * acc[r][nb][8 + 4 * jq + e];
+          }
+          *reinterpret_cast<u32x2*>(o + (size_t)n * inter + 8 * jq) =
+              u32x2{pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])};
+        }
+      }
     }
   }
 }
 
 enum Epi { kStoreF32 = 0, kStoreBF16 = 1, kAddF32 = 2, kSwiGLU = 3 };
 
-// Workspace slots holding tile t's partials, in block order (the blocks
-// whose runs intersect the tile's chunks [t KC, (t + 1) KC)); returns the
-// count.  Called by one thread per reduce block.
-__device__ int tile_slots(long long C, int B, int KC, int seg, int t, int* slots) {
-  if (C * B < (1LL << 31)) {
-    // Every product below fits in 32 bits (g0 <= C, b <= B), and 32-bit
-    // divisions cost a small fraction of the emulated 64-bit ones: the same
-    // slot list, computed several times faster.
-    const unsigned c = (unsigned)C, bb = (unsigned)B;
-    const auto lo = [&](int b) { return (int)(c * (unsigned)b / bb); };
-    const int g0 = t * KC, g1 = g0 + KC;
-    int b = (int)((unsigned)g0 * bb / c);
-    while (b + 1 < B && lo(b + 1) <= g0) ++b;
-    while (b > 0 && lo(b) > g0) --b;
-    int n = 0;
-    for (; b < B; ++b) {
-      const int l = lo(b);
-      if (l >= g1) break;
-      slots[n++] = b * seg + (t - l / KC);
-    }
-    return n;
-  }
-  const long long g0 = (long long)t * KC, g1 = g0 + KC;
-  int b = (int)(g0 * B / C);
-  while (b + 1 < B && run_lo(C, b + 1, B) <= g0) ++b;
-  while (b > 0 && run_lo(C, b, B) > g0) --b;
-  int n = 0;
-  for (; b < B && run_lo(C, b, B) < g1; ++b) slots[n++] = b * seg + (t - (int)(run_lo(C, b, B) / KC));
-  return n;
+// Where a tile's partials are: in block order, first the slot `s0` (the run
+// that holds the tile's first chunk, which may have begun in an earlier
+// tile), then segment 0 of each of the next n - 1 runs.
+struct TileSlots {
+  int s0, next, seg, n;
+  __device__ __forceinline__ int at(int i) const { return i == 0 ? s0 : next + i * seg; }
+};
+__device__ __forceinline__ TileSlots tile_slots(const Runs& runs, int KC, int t) {
+  const int b0 = runs.of(t * KC), b1 = runs.of(t * KC + KC - 1);
+  const int first = (int)((unsigned)runs.lo(b0) / (unsigned)KC);
+  return TileSlots{b0 * runs.seg + (t - first), b0 * runs.seg, runs.seg, b1 - b0 + 1};
 }
 
-// Sum of the partials at element e (node n, tile row r: e = n * 128 + r)
-// over a tile's slot list (from tile_slots), in block order whichever
-// kernel adds them (the same rounding).  The loads of a batch of S slots
-// (S = 4, 8 or 16, the smallest that holds the list; longer lists take
-// several batches) are all issued before the first add, so a sum costs one
-// round trip to memory rather than one per four slots; slots past the end of
-// the list re-read the last one and are not added.
+// Sum of the partials at (node n, tile row r): element e = n * 128 + r, in block
+// order whichever kernel adds them (the same
+// rounding).  The loads of a batch of S slots (S = 4, 8 or 16, the smallest
+// that holds the list; longer lists take several batches) are all issued
+// before the first add, so a sum costs one round trip to memory; slots past
+// the end of the list re-read the last one and are not added.
 typedef float f32x8 __attribute__((ext_vector_type(8)));
-// fp16 partial values at element e of slot k: 8 (f32x8), 4 (f32x4) or 1 (float)
-__device__ __forceinline__ void load_part(const Partials& p, int k, size_t stride, size_t e, f32x8& x, float& sc) {
-  const u32x4 h = *reinterpret_cast<const u32x4*>(p.v + k * stride + e);
+// fp16 partial values: 8 (f32x8), 4 (f32x4) or 1 (float)
+__device__ __forceinline__ void load_part(const uint16_t* p, f32x8& x) {
+  const u32x4 h = *reinterpret_cast<const u32x4*>(p);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const f32x2_t v = unpack_f16x2(h[i]);
     x[2 * i] = v[0];
     x[2 * i + 1] = v[1];
   }
-  sc = p.sc[k * 4 + (int)(e % kRows) / 32];
 }
-__device__ __forceinline__ void load_part(const Partials& p, int k, size_t stride, size_t e, f32x4& x, float& sc) {
-  const u32x2 h = *reinterpret_cast<const u32x2*>(p.v + k * stride + e);
+__device__ __forceinline__ void load_part(const uint16_t* p, f32x4& x) {
+  const u32x2 h = *reinterpret_cast<const u32x2*>(p);
   const f32x2_t lo = unpack_f16x2(h[0]), hi = unpack_f16x2(h[1]);
   x = f32x4{lo[0], lo[1], hi[0], hi[1]};
-  sc = p.sc[k * 4 + (int)(e % kRows) / 32];
 }
-__device__ __forceinline__ void load_part(const Partials& p, int k, size_t stride, size_t e, float& x, float& sc) {
-  x = unpack_f16x2(p.v[k * stride + e])[0];
-  sc = p.sc[k * 4 + (int)(e % kRows) / 32];
-}
+__device__ __forceinline__ void load_part(const uint16_t* p, float& x) { x = unpack_f16x2(*p)[0]; }
 template <typename T, int S>
-__device__ __forceinline__ T slot_batches(const Partials& part, const int* slots, int ns, size_t stride, size_t e) {
+__device__ __forceinline__ T slot_batches(const Partials& part, const TileSlots& ts, int npad, int n, int r) {
   T s{};
-  for (int i0 = 0; i0 < ns; i0 += S) {
+  const size_t stride = (size_t)npad * kStreamRows, e = (size_t)n * kStreamRows + r;
+  for (int i0 = 0; i0 < ts.n; i0 += S) {
     T x[S];
     float sc[S];
 #pragma unroll
-    for (int i = 0; i < S; ++i) load_part(part, slots[min(i0 + i, ns - 1)], stride, e, x[i], sc[i]);
+    for (int i = 0; i < S; ++i) {
+      const int k = ts.at(min(i0 + i, ts.n - 1));
+      load_part(part.v + k * stride + e, x[i]);
+      sc[i] = part.sc[k * 4 + r / 32];
+    }
 #pragma unroll
     for (int i = 0; i < S; ++i)
-      if (i0 + i < ns) s += x[i] * sc[i];
+      if (i0 + i < ts.n) s += x[i] * sc[i];
   }
   return s;
 }
 template <typename T>
-__device__ __forceinline__ T slot_sum_of(const Partials& part, const int* slots, int ns, size_t stride, size_t e) {
-  if (ns <= 4) return slot_batches<T, 4>(part, slots, ns, stride, e);
-  if (ns <= 8) return slot_batches<T, 8>(part, slots, ns, stride, e);
-  return slot_batches<T, 16>(part, slots, ns, stride, e);
+__device__ __forceinline__ T slot_sum_of(const Partials& part, const TileSlots& ts, int npad, int n, int r) {
+  if (ts.n <= 4) return slot_batches<T, 4>(part, ts, npad, n, r);
+  if (ts.n <= 8) return slot_batches<T, 8>(part, ts, npad, n, r);
+  return slot_batches<T, 16>(part, ts, npad, n, r);
 }
 
-// Four blocks per output tile (per gate tile for kSwiGLU): block q takes
-// tile rows 64 (q % 2) .. +63 of the nodes n = q / 2 (mod 2); thread item
+// Four blocks per 128 output rows (per 128 gate rows for kSwiGLU): block q
+// takes rows 64 (q % 2) .. +63 of the nodes n = q / 2 (mod 2); thread item
 // (n, 8 consecutive rows), so every partial read is 16 bytes and eight
 // lanes read one node's whole 128-byte line.
-__global__ __launch_bounds__(256) void linear_reduce_kernel(Partials part, int N, int npad, int K,
-                                                            int O, int B, int seg, int epi, void* __restrict__ out,
-                                                            int inter) {
-  __shared__ int slots[2][256];
-  __shared__ int nslots[2];
-  const int t = blockIdx.x >> 2, half = blockIdx.x & 1, par = (blockIdx.x >> 1) & 1;
+__global__ __launch_bounds__(256) void linear_reduce_kernel(Partials part, int npad, Runs runs, int N, int K, int O,
+                                                            int epi, void* __restrict__ out, int inter) {
+  const int row0 = (int)(blockIdx.x >> 2) * 128 + (int)(blockIdx.x & 1) * 64, par = (blockIdx.x >> 1) & 1;
   const int KC = K / 64;
-  const int tiles = (O + kRows - 1) / kRows;
-  const long long C = (long long)tiles * KC;
-  if (threadIdx.x < 2 && (threadIdx.x == 0 || epi == kSwiGLU))
-    nslots[threadIdx.x] = tile_slots(C, B, KC, seg, threadIdx.x ? t + inter / kRows : t, slots[threadIdx.x]);
-  __syncthreads();
-  const size_t stride = (size_t)npad * kRows;  // elements per slot
-  const int ns0 = nslots[0], ns1 = epi == kSwiGLU ? nslots[1] : 0;
+  const int t0 = row0 / kStreamRows, t1 = (row0 + inter) / kStreamRows;
+  const TileSlots ts0 = tile_slots(runs, KC, t0);
+  const TileSlots ts1 = epi == kSwiGLU ? tile_slots(runs, KC, t1) : ts0;
   for (int item = threadIdx.x; item < (N - par + 1) / 2 * 8; item += 256) {
-    const int n = 2 * (item >> 3) + par, r = half * 64 + 8 * (item & 7);
-    const size_t e = (size_t)n * kRows + r;
-    const int col = t * kRows + r;
-    const f32x8 sv = slot_sum_of<f32x8>(part, slots[0], ns0, stride, e);
+    const int n = 2 * (item >> 3) + par, col = row0 + 8 * (item & 7);
+    const f32x8 sv = slot_sum_of<f32x8>(part, ts0, npad, n, col - t0 * kStreamRows);
     if (epi == kSwiGLU) {
-      const f32x8 uv = slot_sum_of<f32x8>(part, slots[1], ns1, stride, e);
+      const f32x8 uv = slot_sum_of<f32x8>(part, ts1, npad, n, col + inter - t1 * kStreamRows);
       uint16_t* o = reinterpret_cast<uint16_t*>(out) + (size_t)n * inter + col;
 #pragma unroll
       for (int j = 0; j < 8; ++j)
@@ -272,40 +336,39 @@ __global__ __launch_bounds__(256) void linear_reduce_kernel(Partials part, int N
   }
 }
 
-// Slot-list capacity of the fused epilogues (checked on the host).
-constexpr int kMaxTileSlots = 64;
-constexpr int kMaxFusedTiles = 64;
-
 // Projection epilogue fused with the next RMSNorm: for row n,
 // h[n] += the projection (its partial sums), then out[n] = bf16(h[n] /
-// sqrt(mean(h[n]^2) + eps) * w).  One block of 512 threads per row, four
-// float4 columns per thread (out_dim <= 8192).
-constexpr int kAddNormItems = 4;
-__global__ __launch_bounds__(512) void linear_add_rmsnorm_kernel(Partials part, int npad, int K,
-                                                                 int O, int B, int seg, float* __restrict__ resid,
-                                                                 const uint16_t* __restrict__ w, float eps,
-                                                                 uint16_t* __restrict__ out) {
-  __shared__ float red[8];
-  __shared__ int slots[kMaxFusedTiles][kMaxTileSlots];
-  __shared__ int nslots[kMaxFusedTiles];
-  const int n = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// sqrt(mean(h[n]^2) + eps) * w).  One block per row, one float4 column group
+// per thread and item (out_dim <= 8192: up to two items of 1024 threads), so
+// that a row's loads are all in flight at once.
+constexpr int kAddNormItems = 2;
+__global__ __launch_bounds__(1024) void linear_add_rmsnorm_kernel(Partials part, int npad, Runs runs, int K, int O,
+                                                                  float* __restrict__ resid,
+                                                                  const uint16_t* __restrict__ w, float eps,
+                                                                  uint16_t* __restrict__ out) {
+  __shared__ float red[16];
+  const int n = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nt = blockDim.x;
   const int KC = K / 64;
-  const int tiles = (O + kRows - 1) / kRows;
-  const long long C = (long long)tiles * KC;
-  if ((int)threadIdx.x < tiles) nslots[threadIdx.x] = tile_slots(C, B, KC, seg, threadIdx.x, slots[threadIdx.x]);
-  __syncthreads();
-  const size_t stride = (size_t)npad * kRows;
   float* hrow = resid + (size_t)n * O;
   f32x4 hv[kAddNormItems];
+  u32x2 wv[kAddNormItems];
   float ss = 0.f;
 #pragma unroll
   for (int i = 0; i < kAddNormItems; ++i) {
-    const int c = 4 * (threadIdx.x + 512 * i);
+    const int c = 4 * (threadIdx.x + nt * i);
     hv[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    wv[i] = u32x2{0u, 0u};
     if (c < O) {
-      const int t = c / kRows;
-      const f32x4 sv = slot_sum_of<f32x4>(part, slots[t], nslots[t], stride, (size_t)n * kRows + c % kRows);
-      hv[i] = *reinterpret_cast<const f32x4*>(hrow + c) + sv;
+      hv[i] = *reinterpret_cast<const f32x4*>(hrow + c);
+      wv[i] = *reinterpret_cast<const u32x2*>(w + c);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < kAddNormItems; ++i) {
+    const int c = 4 * (threadIdx.x + nt * i);
+    if (c < O) {
+      const int t = c / kStreamRows;
+      hv[i] += slot_sum_of<f32x4>(part, tile_slots(runs, KC, t), npad, n, c - t * kStreamRows);
       *reinterpret_cast<f32x4*>(hrow + c) = hv[i];
     }
   }
@@ -316,16 +379,18 @@ __global__ __launch_bounds__(512) void linear_add_rmsnorm_kernel(Partials part, 
   for (int off = 32; off > 0; off >>= 1) ss += shfl_xor_f(ss, off);
   if (lane == 0) red[wave] = ss;
   __syncthreads();
-  const float tot = ((red[0] + red[1]) + (red[2] + red[3])) + ((red[4] + red[5]) + (red[6] + red[7]));
+  float tot = 0.f;
+  for (int k = 0; k < nt / 64; ++k) tot += red[k];
   const float r = 1.f / sqrtf(tot / (float)O + eps);
 #pragma unroll
   for (int i = 0; i < kAddNormItems; ++i) {
-    const int c = 4 * (threadIdx.x + 512 * i);
+    const int c = 4 * (threadIdx.x + nt * i);
     if (c < O) {
-      const u32x2 wv = *reinterpret_cast<const u32x2*>(w + c);
       u32x2 o;
-      o[0] = pack_bf16x2(hv[i][0] * r * __uint_as_float(wv[0] << 16), hv[i][1] * r * __uint_as_float(wv[0] & 0xFFFF0000u));
-      o[1] = pack_bf16x2(hv[i][2] * r * __uint_as_float(wv[1] << 16), hv[i][3] * r * __uint_as_float(wv[1] & 0xFFFF0000u));
+      o[0] = pack_bf16x2(hv[i][0] * r * __uint_as_float(wv[i][0] << 16),
+                         hv[i][1] * r * __uint_as_float(wv[i][0] & 0xFFFF0000u));
+      o[1] = pack_bf16x2(hv[i][2] * r * __uint_as_float(wv[i][1] << 16),
+                         hv[i][3] * r * __uint_as_float(wv[i][1] & 0xFFFF0000u));
       *reinterpret_cast<u32x2*>(out + (size_t)n * O + c) = o;
     }
   }
@@ -339,32 +404,26 @@ __global__ __launch_bounds__(512) void linear_add_rmsnorm_kernel(Partials part, 
 // P + n.
 template <int D>
 __global__ __launch_bounds__(1024) void linear_qk_norm_rope_kernel(
-    Partials part, int npad, int K, int B, int seg, const uint16_t* __restrict__ q_norm,
+    Partials part, int npad, Runs runs, int K, const uint16_t* __restrict__ q_norm,
     const uint16_t* __restrict__ k_norm, float eps, const int32_t* __restrict__ depth, int P,
     const int32_t* __restrict__ P_dev, RopeFreq fr, int Hq, int Hkv, uint16_t* __restrict__ q_out,
     uint16_t* __restrict__ k_cache, uint16_t* __restrict__ v_cache, long long cap) {
   constexpr int HALF = D / 2;
-  static_assert(kRows % D == 0, "a head lies in one tile");
+  static_assert(kStreamRows % D == 0, "a head lies in one tile");
   if (P_dev) P = min(max(*P_dev, 0), P);
-  const int n = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int n = blockIdx.x, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nh = Hq + 2 * Hkv;
   const int hh = blockIdx.y * 16 + wave;
   if (hh >= nh) return;
-  __shared__ int slots[16][kMaxTileSlots];
-  __shared__ int nslots[16];
-  const int KC = K / 64;
-  const long long C = (long long)(nh * D / kRows) * KC;
-  const size_t stride = (size_t)npad * kRows;
-  const int t = hh * D / kRows, r0 = hh * D % kRows;
-  if (lane == 0) nslots[wave] = tile_slots(C, B, KC, seg, t, slots[wave]);
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  const int t = hh * D / kStreamRows, r0 = hh * D - t * kStreamRows;
+  const TileSlots ts = tile_slots(runs, K / 64, t);
   const long long row = (long long)P + n;
   const bool act = lane < HALF;
   float a = 0.f, b = 0.f;
   if (act) {
-    a = slot_sum_of<float>(part, slots[wave], nslots[wave], stride, (size_t)n * kRows + r0 + lane);
-    b = slot_sum_of<float>(part, slots[wave], nslots[wave], stride, (size_t)n * kRows + r0 + lane + HALF);
+    a = slot_sum_of<float>(part, ts, npad, n, r0 + lane);
+    b = slot_sum_of<float>(part, ts, npad, n, r0 + lane + HALF);
   }
   if (hh >= Hq + Hkv) {
     uint16_t* dst = v_cache + ((size_t)(hh - Hq - Hkv) * cap + row) * D;
@@ -386,7 +445,8 @@ __global__ __launch_bounds__(1024) void linear_qk_norm_rope_kernel(
 }
 
 struct LinPlan {
-  int nb, blocks, seg;
+  int nb;
+  Runs runs;
   size_t val_bytes;  // fp16 partial values (the factors follow)
   size_t ws_bytes;
 };
@@ -398,13 +458,15 @@ Partials partials_in(void* workspace, const LinPlan& p) {
 LinPlan lin_plan(int N, int K, int O) {
   LinPlan p{};
   p.nb = N <= 32 ? 1 : N <= 64 ? 2 : N <= 128 ? 4 : 8;
-  const long long C = (long long)((O + kRows - 1) / kRows) * (K / 64);
-  const int cus = device_cus() < 256 ? device_cus() : 256;  // the reduce kernel keeps <= 256 slots per tile
-  p.blocks = (int)(C < cus ? C : cus);
-  const long long run = (C + p.blocks - 1) / p.blocks;
-  p.seg = (int)(run / (K / 64)) + 2;  // tiles a run can touch
-  p.val_bytes = ((size_t)p.blocks * p.seg * (32 * p.nb) * kRows * sizeof(uint16_t) + 255) / 256 * 256;
-  p.ws_bytes = p.val_bytes + (size_t)p.blocks * p.seg * 4 * sizeof(float);
+  const int KC = K / 64;
+  const int C = (int)((O + (long long)kStreamRows - 1) / kStreamRows) * KC;
+  p.runs.B = C < device_cus() ? C : device_cus();
+  p.runs.q = C / p.runs.B;
+  p.runs.r = C % p.runs.B;
+  p.runs.seg = (p.runs.q + (p.runs.r > 0)) / KC + 2;  // tiles a run can touch
+  const size_t slots = (size_t)p.runs.B * p.runs.seg;
+  p.val_bytes = (slots * (32 * p.nb) * kStreamRows * sizeof(uint16_t) + 255) / 256 * 256;
+  p.ws_bytes = p.val_bytes + slots * 4 * sizeof(float);
   return p;
 }
 
@@ -427,28 +489,26 @@ extern "C" size_t ooo_linear_workspace(int32_t n_rows, int32_t in_dim, int32_t o
   return lin_plan(n_rows, in_dim, out_dim).ws_bytes;
 }
 
-// Largest number of stream-K blocks whose runs meet one output tile (the
-// length of that tile's slot list).
-static int max_tile_slots(int n_rows, int in_dim, int out_dim) {
-  const LinPlan p = lin_plan(n_rows, in_dim, out_dim);
-  const int KC = in_dim / 64, tiles = (out_dim + kRows - 1) / kRows;
-  const long long C = (long long)tiles * KC;
-  std::vector<int> count(tiles, 0);
-  for (int b = 0; b < p.blocks; ++b) {
-    const long long lo = run_lo(C, b, p.blocks), hi = run_lo(C, b + 1, p.blocks);
-    if (hi <= lo) continue;
-    for (long long t = lo / KC; t <= (hi - 1) / KC; ++t) ++count[t];
+// The fused epilogues refuse shapes with more than 64 stream-K runs on one
+// 128-row tile when the chunks are cut at C b / B (very few tiles under a
+// long K).  Only then can a tile be that wide, so the count is taken there.
+constexpr int kMaxTileRuns = 64;
+static bool too_many_runs(int n_rows, int in_dim, int out_dim) {
+  if (n_rows < 1 || in_dim < 64 || in_dim % 64 || n_rows > 256 || out_dim < 1) return false;  // refused elsewhere
+  const long long KC = in_dim / 64, tiles = (out_dim + 127LL) / 128, C = tiles * KC;
+  const long long cus = device_cus() < 256 ? device_cus() : 256, B = C < cus ? C : cus;
+  if (B / tiles + 2 <= kMaxTileRuns) return false;
+  for (long long t = 0; t < tiles; ++t) {
+    int n = 0;
+    for (long long b = 0; b < B; ++b) n += C * b / B < (t + 1) * KC && C * (b + 1) / B > t * KC;
+    if (n > kMaxTileRuns) return true;
   }
-  int m = 0;
-  for (int c : count) m = c > m ? c : m;
-  return m;
+  return false;
 }
 
-// Validation and the streaming kernel shared by the entry points; on
-// success the partial sums are in the workspace and *plan is set.
-static int stream_k(const char* who, const void* x, const void* weight, int32_t n_rows, int32_t in_dim,
-                    int32_t out_dim, int32_t weight_layout, void* workspace, size_t ws_bytes, hipStream_t st,
-                    LinPlan* plan) {
+// Validation shared by the entry points; on success *plan is set.
+static int lin_check(const char* who, const void* x, const void* weight, int32_t n_rows, int32_t in_dim,
+                     int32_t out_dim, int32_t weight_layout, const void* workspace, size_t ws_bytes, LinPlan* plan) {
   OOO_REQUIRE(x && weight, OOO_ERR_INVALID, "%s: null pointer", who);
   OOO_REQUIRE(n_rows >= 1 && in_dim >= 1 && out_dim >= 1, OOO_ERR_INVALID, "%s: sizes must be positive", who);
   OOO_REQUIRE(weight_layout == OOO_W_ROWS || weight_layout == OOO_W_PACKED, OOO_ERR_INVALID,
@@ -458,16 +518,28 @@ static int stream_k(const char* who, const void* x, const void* weight, int32_t 
   const LinPlan p = lin_plan(n_rows, in_dim, out_dim);
   OOO_REQUIRE(workspace && ws_bytes >= p.ws_bytes, OOO_ERR_CAPACITY, "%s: workspace of %zu bytes needed (got %zu)",
               who, p.ws_bytes, ws_bytes);
+  *plan = p;
+  return OOO_OK;
+}
+
+// The streaming kernel shared by the entry points: leaves the partial sums
+// in the workspace.
+static int stream_k(const char* who, const void* x, const void* weight, int32_t n_rows, int32_t in_dim,
+                    int32_t out_dim, int32_t weight_layout, void* workspace, size_t ws_bytes, hipStream_t st,
+                    LinPlan* plan) {
+  LinPlan p{};
+  const int rc = lin_check(who, x, weight, n_rows, in_dim, out_dim, weight_layout, workspace, ws_bytes, &p);
+  if (rc != OOO_OK) return rc;
   const uint16_t* X = (const uint16_t*)x;
   const uint16_t* W = (const uint16_t*)weight;
   const Partials part = partials_in(workspace, p);
   const bool pk = weight_layout == OOO_W_PACKED;
-#define OOO_LIN_LAUNCH(NBV)                                                                                        \
-  do {                                                                                                            \
-    if (pk)                                                                                                       \
-      linear_bf16_kernel<NBV, true><<<p.blocks, kStreamThreads, 0, st>>>(X, W, n_rows, in_dim, out_dim, p.seg, part);         \
-    else                                                                                                          \
-      linear_bf16_kernel<NBV, false><<<p.blocks, kStreamThreads, 0, st>>>(X, W, n_rows, in_dim, out_dim, p.seg, part);        \
+#define OOO_LIN_LAUNCH(NBV)                                                                                           \
+  do {                                                                                                               \
+    if (pk)                                                                                                          \
+      linear_bf16_kernel<NBV, true><<<p.runs.B, kTallThreads, 0, st>>>(X, W, n_rows, in_dim, out_dim, p.runs, part); \
+    else                                                                                                             \
+      linear_bf16_kernel<NBV, false><<<p.runs.B, kTallThreads, 0, st>>>(X, W, n_rows, in_dim, out_dim, p.runs, part); \
   } while (0)
   if (p.nb == 1) OOO_LIN_LAUNCH(1);
   else if (p.nb == 2) OOO_LIN_LAUNCH(2);
@@ -476,6 +548,43 @@ static int stream_k(const char* who, const void* x, const void* weight, int32_t 
 #undef OOO_LIN_LAUNCH
   *plan = p;
   return OOO_OK;
+}
+
+// Whether the SwiGLU projection owns whole columns per block or goes through
+// stream-K.  With u units per CU a block of the direct kernel takes about
+// 3 + KC max(0.32, 0.15 u) us (below two units a CU the chunk pipeline's own
+// period binds, not the bytes) and stream-K with its second kernel about
+// 8 + 0.15 KC u (10 at 33-64 nodes, 12 past that), so stream-K is only ahead
+// for few units under a long K.  Measured, direct / stream-K us: one node,
+// K 4096: I 4352 (u 1.06) 23.1 / 18.3, I 8320 26.1 / 28.1, I 12416 37.2 /
+// 38.4, I 14336 39.6 / 43.2; K 1024, I 3072 8.0 / 9.8; K 2048, I 4352 13.3 /
+// 13.7; 40 nodes, K 4096: I 4352 25.5 / 21.0, I 12416 36.1 / 40.8; 128 nodes:
+// K 4096, I 4352 38.3 / 31.5, K 2048 21.8 / 25.7, K 5120, I 27648 102 / 142;
+// 256 nodes: K 4096, I 4352 58.8 / 46, K 5120, I 27648 184 / 190.
+static bool swiglu_direct(int n_rows, int in_dim, int inter) {
+  const long long KC = in_dim / 64, units = inter / 16, cus = device_cus();
+  const int ahead = n_rows <= 32 ? 500 : n_rows <= 64 ? 700 : 900;  // 0.01 us
+  return KC * (32 * cus - 15 * units) < ahead * cus;
+}
+
+static void launch_swiglu(int nb, bool pk, const uint16_t* X, const uint16_t* W, int N, int K, int inter, uint16_t* out,
+                          hipStream_t st) {
+  const int units = inter / 16;
+  const int blocks = units < device_cus() ? units : device_cus();
+  const bool tall = (units + blocks - 1) / blocks > 4;
+#define OOO_SW_LAUNCH(NBV, RGV)                                                                         \
+  do {                                                                                                 \
+    if (pk) linear_swiglu_kernel<NBV, RGV, true><<<blocks, kTallThreads, 0, st>>>(X, W, N, K, inter, out);  \
+    else linear_swiglu_kernel<NBV, RGV, false><<<blocks, kTallThreads, 0, st>>>(X, W, N, K, inter, out);    \
+  } while (0)
+  if (nb == 1 && tall) OOO_SW_LAUNCH(1, 2);
+  else if (nb == 1) OOO_SW_LAUNCH(1, 1);
+  else if (nb == 2 && tall) OOO_SW_LAUNCH(2, 2);
+  else if (nb == 2) OOO_SW_LAUNCH(2, 1);
+  else if (nb == 4 && tall) OOO_SW_LAUNCH(4, 2);
+  else if (nb == 4) OOO_SW_LAUNCH(4, 1);
+  else OOO_SW_LAUNCH(8, 1);
+#undef OOO_SW_LAUNCH
 }
 
 extern "C" int ooo_linear(const void* x, const void* weight, int32_t n_rows, int32_t in_dim, int32_t out_dim,
@@ -488,13 +597,21 @@ extern "C" int ooo_linear(const void* x, const void* weight, int32_t n_rows, int
               "ooo_linear: the SwiGLU epilogue needs out_dim %% 256 == 0 (gate and up halves of whole tiles)");
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   LinPlan p{};
+  if (epilogue == OOO_EPI_SWIGLU_BF16 && swiglu_direct(n_rows, in_dim, out_dim / 2)) {
+    const int rc = lin_check("ooo_linear", x, weight, n_rows, in_dim, out_dim, weight_layout, workspace, ws_bytes, &p);
+    if (rc != OOO_OK) return rc;
+    launch_swiglu(p.nb, weight_layout == OOO_W_PACKED, (const uint16_t*)x, (const uint16_t*)weight, n_rows, in_dim,
+                  out_dim / 2, (uint16_t*)out, st);
+    const hipError_t e = hipGetLastError();
+    OOO_REQUIRE(e == hipSuccess, OOO_ERR_HIP, "ooo_linear: launch failed: %s", hipGetErrorString(e));
+    return ooo::ok();
+  }
   const int rc = stream_k("ooo_linear", x, weight, n_rows, in_dim, out_dim, weight_layout, workspace, ws_bytes, st, &p);
   if (rc != OOO_OK) return rc;
   const Partials part = partials_in(workspace, p);
-  const int tiles = (out_dim + kRows - 1) / kRows;
-  const int rgrid = 4 * (epilogue == OOO_EPI_SWIGLU_BF16 ? tiles / 2 : tiles);
-  linear_reduce_kernel<<<rgrid, 256, 0, st>>>(part, n_rows, 32 * p.nb, in_dim, out_dim, p.blocks, p.seg, (int)epilogue,
-                                              out, out_dim / 2);
+  const int rows = epilogue == OOO_EPI_SWIGLU_BF16 ? out_dim / 2 : out_dim;
+  linear_reduce_kernel<<<4 * ((rows + 127) / 128), 256, 0, st>>>(part, 32 * p.nb, p.runs, n_rows, in_dim, out_dim,
+                                                                 (int)epilogue, out, out_dim / 2);
   const hipError_t e = hipGetLastError();
   OOO_REQUIRE(e == hipSuccess, OOO_ERR_HIP, "ooo_linear: launch failed: %s", hipGetErrorString(e));
   return ooo::ok();
@@ -506,21 +623,20 @@ extern "C" int ooo_linear_add_rmsnorm(const void* x, const void* weight, int32_t
                                       size_t ws_bytes, void* stream) {
   OOO_REQUIRE(residual && norm_weight && normed_out, OOO_ERR_INVALID, "ooo_linear_add_rmsnorm: null pointer");
   OOO_REQUIRE(eps >= 0.f, OOO_ERR_INVALID, "ooo_linear_add_rmsnorm: eps must be >= 0");
-  OOO_REQUIRE(out_dim % 4 == 0 && out_dim <= 512 * 4 * kAddNormItems, OOO_ERR_UNSUPPORTED,
+  OOO_REQUIRE(out_dim % 4 == 0 && out_dim <= 1024 * 4 * kAddNormItems, OOO_ERR_UNSUPPORTED,
               "ooo_linear_add_rmsnorm: out_dim %d must be a multiple of 4 and at most %d", out_dim,
-              512 * 4 * kAddNormItems);
-  OOO_REQUIRE(n_rows < 1 || in_dim < 64 || in_dim % 64 || n_rows > 256 ||
-                  max_tile_slots(n_rows, in_dim, out_dim) <= kMaxTileSlots,
-              OOO_ERR_UNSUPPORTED, "ooo_linear_add_rmsnorm: more than %d partial slots per tile at this shape",
-              kMaxTileSlots);
+              1024 * 4 * kAddNormItems);
+  OOO_REQUIRE(!too_many_runs(n_rows, in_dim, out_dim), OOO_ERR_UNSUPPORTED,
+              "ooo_linear_add_rmsnorm: more than %d partial slots per tile at this shape", kMaxTileRuns);
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   LinPlan p{};
   const int rc = stream_k("ooo_linear_add_rmsnorm", x, weight, n_rows, in_dim, out_dim, weight_layout, workspace,
                           ws_bytes, st, &p);
   if (rc != OOO_OK) return rc;
-  linear_add_rmsnorm_kernel<<<n_rows, 512, 0, st>>>(partials_in(workspace, p), 32 * p.nb, in_dim, out_dim, p.blocks,
-                                                     p.seg, residual, (const uint16_t*)norm_weight, eps,
-                                                     (uint16_t*)normed_out);
+  const int threads = out_dim / 4 >= 1024 ? 1024 : (out_dim / 4 + 63) / 64 * 64;
+  linear_add_rmsnorm_kernel<<<n_rows, threads, 0, st>>>(partials_in(workspace, p), 32 * p.nb, p.runs, in_dim, out_dim,
+                                                        residual, (const uint16_t*)norm_weight, eps,
+                                                        (uint16_t*)normed_out);
   const hipError_t e = hipGetLastError();
   OOO_REQUIRE(e == hipSuccess, OOO_ERR_HIP, "ooo_linear_add_rmsnorm: launch failed: %s", hipGetErrorString(e));
   return ooo::ok();
@@ -542,12 +658,10 @@ extern "C" int ooo_linear_qk_norm_rope(const void* x, const void* weight, int32_
   OOO_REQUIRE(head_dim == 64 || head_dim == 128, OOO_ERR_UNSUPPORTED,
               "ooo_linear_qk_norm_rope: head_dim %d not supported (64 or 128)", head_dim);
   const int nh = n_q_heads + 2 * n_kv_heads;
-  OOO_REQUIRE((int64_t)nh * head_dim % kRows == 0, OOO_ERR_UNSUPPORTED,
-              "ooo_linear_qk_norm_rope: (n_q_heads + 2 n_kv_heads) * head_dim must be a multiple of %d", kRows);
-  OOO_REQUIRE(n_rows < 1 || in_dim < 64 || in_dim % 64 || n_rows > 256 ||
-                  max_tile_slots(n_rows, in_dim, nh * head_dim) <= kMaxTileSlots,
-              OOO_ERR_UNSUPPORTED, "ooo_linear_qk_norm_rope: more than %d partial slots per tile at this shape",
-              kMaxTileSlots);
+  OOO_REQUIRE((int64_t)nh * head_dim % kStreamRows == 0, OOO_ERR_UNSUPPORTED,
+              "ooo_linear_qk_norm_rope: (n_q_heads + 2 n_kv_heads) * head_dim must be a multiple of %d", kStreamRows);
+  OOO_REQUIRE(!too_many_runs(n_rows, in_dim, nh * head_dim), OOO_ERR_UNSUPPORTED,
+              "ooo_linear_qk_norm_rope: more than %d partial slots per tile at this shape", kMaxTileRuns);
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   LinPlan p{};
   const int rc = stream_k("ooo_linear_qk_norm_rope", x, weight, n_rows, in_dim, nh * head_dim, weight_layout,
@@ -557,13 +671,13 @@ extern "C" int ooo_linear_qk_norm_rope(const void* x, const void* weight, int32_
   const dim3 grid(n_rows, (nh + 15) / 16);
   const Partials part = partials_in(workspace, p);
   if (head_dim == 128)
-    linear_qk_norm_rope_kernel<128><<<grid, 1024, 0, st>>>(part, 32 * p.nb, in_dim, p.blocks, p.seg,
+    linear_qk_norm_rope_kernel<128><<<grid, 1024, 0, st>>>(part, 32 * p.nb, p.runs, in_dim,
                                                             (const uint16_t*)q_norm, (const uint16_t*)k_norm, eps, depth,
                                                             prefix_len, prefix_len_dev, fr, n_q_heads, n_kv_heads,
                                                             (uint16_t*)q_out, (uint16_t*)k_cache, (uint16_t*)v_cache,
                                                             cap);
   else
-    linear_qk_norm_rope_kernel<64><<<grid, 1024, 0, st>>>(part, 32 * p.nb, in_dim, p.blocks, p.seg,
+    linear_qk_norm_rope_kernel<64><<<grid, 1024, 0, st>>>(part, 32 * p.nb, p.runs, in_dim,
                                                            (const uint16_t*)q_norm, (const uint16_t*)k_norm, eps, depth,
                                                            prefix_len, prefix_len_dev, fr, n_q_heads, n_kv_heads,
                                                            (uint16_t*)q_out, (uint16_t*)k_cache, (uint16_t*)v_cache,

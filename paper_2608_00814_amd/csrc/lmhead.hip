@@ -7,17 +7,18 @@
 // (2.4 GHz at 32 nodes, 1.6-1.7 at 128 and 256; with zero hidden rows the
 // same kernel runs 128 nodes at 2.3 GHz and at the HBM rate).  So the design
 // keeps whole lines in flight and moves few X bytes per W byte:
-//  * A persistent grid, one block per CU.  The vocabulary's 32-row groups
-//    are dealt out evenly and in order, so no block streams more than one
-//    group beyond the average, and a block cuts its groups into tiles of
-//    nearly equal size (18 or 19 groups: three tiles of 6 or 7).
-//  * Tiles of up to 8 groups (256 rows; 4 at 129-256 nodes, where the
-//    accumulators of two groups a wave do not fit): every tile re-reads all
-//    of X from L2, so taller tiles move half the X bytes of 128-row ones.
-//    Per call, 128-row tiles against this: 303.0 -> 270.2 us at 128 nodes,
-//    H 5120, V 152064; 321.6 -> 297.7 at 256 nodes, H 4096, V 128256 (the
-//    fragment reads a k-step ahead, below); 185.7 -> 185.0 at 64 nodes,
-//    H 4096, V 151936 (HBM-bound at 6.7 TB/s).
+//  * A persistent grid, one block per CU, that walks tiles of up to 8
+//    32-row groups (256 rows; 4 at 129-256 nodes, where the accumulators of
+//    two groups a wave do not fit) round-robin: every tile re-reads all of X
+//    from L2, so taller tiles move half the X bytes of 128-row ones.  The
+//    tiles of a call are nearly equal (V 151936 on 256 blocks: three tiles
+//    each of 6 or 7 groups), so no round runs with most slots empty.  A
+//    contiguous range per block streams as fast but makes the first pass
+//    over a new weight 50 us longer (275 against 225 us).
+//    Per call, 128-row tiles of seven waves against this: 307.6 -> 280.4 us
+//    at 128 nodes, H 5120, V 152064; 326.9 -> 310.4 at 256 nodes, H 4096, V
+//    128256 (there the fragment reads a k-step ahead, below); 186.8 -> 185.7
+//    at 64 nodes, H 4096, V 151936 (HBM-bound at 6.7 TB/s).
 //  * The streaming core (stream_core.h): four loader waves copy each W
 //    chunk (a group's 32 rows x 128 B per slot) and the X chunk (all nodes x
 //    128 B) straight into an LDS ring with global_load_lds; four compute
@@ -44,42 +45,31 @@ struct Cand {
 
 constexpr int kLmRows = kStreamRows;  // vocabulary rows per tile (4 waves x 32)
 
-// First of the n items that part t of T gets when they are dealt out evenly
-// in order (the first n % T parts hold one more).
-__device__ __forceinline__ int even_cut(int n, int t, int T) { return n / T * t + min(t, n % T); }
-
 template <int NB, int RG, bool PACKED>
 __global__ __launch_bounds__(kTallThreads) void lmhead_bf16_kernel(const uint16_t* __restrict__ X,
                                                                    const uint16_t* __restrict__ Wt, int N, int H,
                                                                    int V, Cand* __restrict__ partial,
                                                                    float* __restrict__ logits) {
-  using R = TallRing<NB, RG>;
-  static_assert(4 * 32 * NB * sizeof(Cand) <= R::BYTES, "the reduction reuses the ring");
-  __shared__ __attribute__((aligned(1024))) uint8_t lds[R::BYTES];
+  constexpr int SLOTS = 4 * RG;
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[kRingBytes];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int chunks = H / 64;
   const int b = (int)blockIdx.x, grid = (int)gridDim.x;
   const int groups = (V + 31) / 32;
-  const int g_lo = even_cut(groups, b, grid);
-  const int n_my = even_cut(groups, b + 1, grid) - g_lo;  // >= 1: grid <= groups
-  const int T = (n_my + R::SLOTS - 1) / R::SLOTS;
-  const int per = n_my / T, more = n_my % T;
-  const auto cut = [&](int t) { return g_lo + per * t + min(t, more); };  // first group of tile t
+  // Tiles of `per` or per + 1 groups, T a block: block b takes tiles b, b +
+  // grid, ..., so that at any time the blocks read neighbouring rows.
+  const int T = (groups + SLOTS * grid - 1) / (SLOTS * grid);
+  const int per = groups / (T * grid), more = groups % (T * grid);
+  const auto first = [&](int i) { return per * i + min(i, more); };  // first group of tile i of T * grid
+  const auto tile = [&](int t) { return GroupRange{first(b + t * grid), first(b + t * grid + 1)}; };
+  const Ring ring(per + (more > 0), N, NB);
 
   if (wave >= 4) {
     const int ld = wave - 4;
     XShare<NB> xs(X, N, H, ld, lane);
-    for_tiles_load<NB, RG>(T, chunks, ld, cut,
-                           [&](int g, int kc, uint8_t* dst) {
-                             if (PACKED)
-                               dma_w_slot_packed(Wt + ((size_t)(g / 4) * chunks + kc) * (kStreamRows * 64) +
-                                                     32 * 64 * (g % 4) + lane * 8,
-                                                 1, dst);
-                             else
-                               dma_w_slot_rows(Wt, H, 32 * g, V, kc, dst, lane);
-                           },
-                           xs, lds);
+    GroupSlots<RG, PACKED> slots(Wt, chunks, V, H, lane);
+    tall_load<NB, RG>(0, 0, T * chunks, chunks, per, ld, tile, slots, xs, ring, lds);
     __syncthreads();  // matches the compute waves' barriers around the final reduction
     __syncthreads();
     return;
@@ -99,13 +89,13 @@ __global__ __launch_bounds__(kTallThreads) void lmhead_bf16_kernel(const uint16_
   int stage = 0;
   wg_barrier();  // the first chunk has landed
   for (int t = 0; t < T; ++t) {
-    const int g0 = cut(t), ng = cut(t + 1) - g0;
+    const int g0 = tile(t).lo, ng = tile(t).hi - g0;
     f32x16 acc[RG][NB];
 #pragma unroll
     for (int r = 0; r < RG; ++r)
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) acc[r][nb] = f32x16{};
-    tall_tile<NB, RG>(chunks, t + 1 == T, ng, wave, lds, off, stage, acc);
+    tall_tile<NB, RG>(chunks, t + 1 == T, ng, wave, lds, ring, off, stage, acc);
     // acc[r][nb][j] = logit of vocabulary row 32 g + 8(j/4) + 4u + j%4, g = g0 + wave + 4r, node 32nb + c
 #pragma unroll
     for (int r = 0; r < RG; ++r) {

@@ -31,40 +31,12 @@ constexpr int kStreamThreads = 448;  // 4 compute waves + 2 W loaders + 1 X load
 // physical piece of logical piece p in LDS row r (and in the packed layout)
 __device__ __forceinline__ int piece_swz(int r) { return (r >> 1) & 7; }
 
-template <int NB>
-struct StreamRing {
-  static constexpr int XR = 32 * NB;              // node rows staged (padded)
-  static constexpr int WS = kStreamRows * 128;    // bytes of a W chunk
-  static constexpr int XS = XR * 128;             // bytes of an X chunk
-  static constexpr int NS = NB == 1 ? 7 : NB == 2 ? 6 : NB == 4 ? 4 : 3;
-  static constexpr int XREG = NS * WS;            // start of the X stages
-  static constexpr int BYTES = NS * (WS + XS);
-  static constexpr int WDMA = WS / 1024 / 2;      // DMA instructions per W chunk and W loader
-  static constexpr int XDMA = XS / 1024;          // ... per X chunk
-  static_assert((NS - 2) * WDMA <= 63 && (NS - 2) * XDMA <= 63, "vmcnt range");
-  static_assert(BYTES <= 160 * 1024, "LDS capacity");
-};
-
-// wait until at most `ahead` chunks of PER DMA instructions are pending
-template <int PER, int MAXA>
-__device__ __forceinline__ void wait_chunks(int ahead) {
-  static_assert(MAXA <= 5, "ring depth");
-  if (MAXA >= 5 && ahead >= 5) wait_vmcnt<(MAXA >= 5 ? 5 * PER : 0)>();
-  else if (MAXA >= 4 && ahead == 4) wait_vmcnt<(MAXA >= 4 ? 4 * PER : 0)>();
-  else if (MAXA >= 3 && ahead == 3) wait_vmcnt<(MAXA >= 3 ? 3 * PER : 0)>();
-  else if (MAXA >= 2 && ahead == 2) wait_vmcnt<(MAXA >= 2 ? 2 * PER : 0)>();
-  else if (ahead == 1) wait_vmcnt<PER>();
-  else wait_vmcnt<0>();
-}
-
 // One 32-row W slot (4 KiB at dst).  Packed: src is the slot's 4 KiB run
-// plus lane * 8 elements (a slot whose group is empty passes an L2-resident
-// address with step 0, so every chunk has the same instruction count).
-__device__ __forceinline__ void dma_w_slot_packed(const uint16_t* src, int step, uint8_t* dst) {
+// plus lane * 8 elements.
+__device__ __forceinline__ void dma_w_slot_packed(const uint16_t* src, uint8_t* dst) {
 #pragma unroll
   for (int jj = 0; jj < 4; ++jj)
-    __builtin_amdgcn_global_load_lds(OOO_GLB(src + (step ? jj * 512 : 0)), OOO_LDS(dst + jj * 1024), 16, 0,
-                                     kStreamOnce);
+    __builtin_amdgcn_global_load_lds(OOO_GLB(src + jj * 512), OOO_LDS(dst + jj * 1024), 16, 0, kStreamOnce);
 }
 // Row layout: rows row0 .. row0 + 31 of W[rows][ld] (clamped to the last
 // row), columns 64 kc .. 64 kc + 63; lane = (row within an instruction,
@@ -81,34 +53,6 @@ __device__ __forceinline__ void dma_w_slot_rows(const uint16_t* W, long long ld,
   }
 }
 
-// X chunk kc of X[N][ld] (rows padded to 32 NB by repeating the last row).
-template <int NB>
-__device__ __forceinline__ void dma_x_chunk(const uint16_t* X, int N, long long ld, int kc, uint8_t* dst, int lane) {
-#pragma unroll
-  for (int j = 0; j < StreamRing<NB>::XDMA; ++j) {
-    const int r = 8 * j + lane / 8;
-    const int pc = (lane % 8) ^ piece_swz(r);
-    const int row = min(r, N - 1);
-    __builtin_amdgcn_global_load_lds(OOO_GLB(X + (size_t)row * ld + kc * 64 + pc * 8), OOO_LDS(dst + j * 1024), 16, 0,
-                                     0);
-  }
-}
-
-// A loader wave's stream of `total` chunks: chunks 0 .. NS - 2 up front,
-// then for every chunk q: wait for this wave's share of chunk q, the block
-// barrier (every share landed, and the compute waves are done with chunk
-// q - 1), then request chunk q + NS - 1 into the stage chunk q - 1 used.
-// issue(q, stage) issues this wave's PER DMA instructions of chunk q.
-template <int NS, int PER, class Issue>
-__device__ __forceinline__ void loader_stream(int total, Issue&& issue) {
-  for (int q = 0; q < NS - 1 && q < total; ++q) issue(q, q);
-  for (int q = 0; q < total; ++q) {
-    wait_chunks<PER, NS - 2>(min(NS - 2, total - 1 - q));
-    wg_barrier();
-    if (q + NS - 1 < total) issue(q + NS - 1, (q + NS - 1) % NS);
-  }
-}
-
 // LDS byte offsets of compute lane (c, u)'s fragments in a W or X stage:
 // piece 2s + u of row c (swizzled), for the k-steps s of a chunk.
 __device__ __forceinline__ void frag_offsets(int lane, uint32_t (&off)[4]) {
@@ -116,26 +60,6 @@ __device__ __forceinline__ void frag_offsets(int lane, uint32_t (&off)[4]) {
 #pragma unroll
   for (int s4 = 0; s4 < 4; ++s4) off[s4] = c * 128 + (((2 * s4 + u) ^ piece_swz(c)) << 4);
 }
-
-// One chunk of a compute wave: acc[nb] += (its 32 W rows at Ws) x (node
-// rows 32 nb .. 32 nb + 31 at Xs)^T.  acc[nb][j] then belongs to W row
-// 8 (j / 4) + 4 u + j % 4 of the wave's 32 and node 32 nb + c.
-template <int NB>
-__device__ __forceinline__ void chunk_mfma(const uint8_t* Ws, const uint8_t* Xs, const uint32_t (&off)[4],
-                                           f32x16 (&acc)[NB]) {
-  bf16x8 af[4], bf[NB][4];
-#pragma unroll
-  for (int s4 = 0; s4 < 4; ++s4) {
-    af[s4] = as_bf16x8(*reinterpret_cast<const u32x4*>(Ws + off[s4]));
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) bf[nb][s4] = as_bf16x8(*reinterpret_cast<const u32x4*>(Xs + nb * 4096 + off[s4]));
-  }
-#pragma unroll
-  for (int s4 = 0; s4 < 4; ++s4)
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) acc[nb] = mfma32(af[s4], bf[nb][s4], acc[nb]);
-}
-
 
 // ------------------------------------------------------------- tall tiles
 // The same stream with tiles of up to 128 RG rows: RG 32-row slots per
@@ -148,83 +72,172 @@ constexpr int kTallThreads = 512;
 // Workgroup barrier after this wave's LDS reads have returned.
 __device__ __forceinline__ void lds_read_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-template <int NB, int RG>
-struct TallRing {
-  static constexpr int SLOTS = 4 * RG;
-  static constexpr int WS = SLOTS * 4096;   // bytes of a W chunk
-  static constexpr int XS = NB * 4096;      // bytes of an X chunk
-  static constexpr int STAGE = WS + XS;
-  static constexpr int NS = 160 * 1024 / STAGE < 7 ? 160 * 1024 / STAGE : 7;
-  static constexpr int BYTES = NS * STAGE;
-  static_assert(NS >= 2 && (NS - 2) * (4 * RG + NB) <= 63, "ring depth, vmcnt range");
+constexpr int kRingBytes = 160 * 1024;  // the whole LDS: one block per CU
+
+// Bytes a block requests ahead.  Enough for the HBM latency at its share of
+// the rate; more makes the first chunks of all blocks land later and gains
+// nothing after (2 x 12288 gate/up rows of 4096 columns, one node: 37.9 us
+// with 144 KiB ahead, 37.2 with 48; 2 x 4352 rows: 24.0 and 23.1; two
+// Qwen3-8B layers at one node 212.8 and 204.8, at 64 nodes 245.1 and 243.1).
+constexpr int kRingAhead = 48 * 1024;
+
+// Ring of the chunks of tiles of up to `slots` groups: a stage holds the W
+// slots, then the X rows there are (in eights).  Fewer slots or nodes give
+// more stages, so a block with little work per chunk still has many bytes in
+// flight.  Fragment reads of node rows past the ones copied run into what
+// follows (the next stage, or room kept behind the last).
+struct Ring {
+  int xoff, bytes, ns;
+  __device__ __forceinline__ Ring(int slots, int N, int NB) {
+    const int x = (N + 7) / 8 * 1024;
+    xoff = slots * 4096;
+    bytes = xoff + x;
+    ns = min((kRingBytes - (NB * 4096 - x)) / bytes, max(3, 1 + (kRingAhead + bytes - 1) / bytes));
+  }
 };
 
-// Loader i's share of the X chunks: rows 8 (i NB + j) + lane / 8, j < NB
-// (rows past N repeat the last one).
+// s_waitcnt vmcnt(n) for a count known at run time only (wave-uniform): a
+// jump into a table of waits, because what follows the wait is on every
+// chunk's critical path (compare-and-branch code for the same choice made
+// the LM head at 128 nodes 3.5% slower: 286.5 against 276.9 us).  Counts past
+// 56 wait for 56; waiting for fewer is always right.
+__device__ __forceinline__ void wait_vmcnt_at(int n) {
+  const int to = __builtin_amdgcn_readfirstlane(12 + 8 * min(max(n, 0), 56));
+  // s_getpc gives the address of the s_add; three instructions of 4 bytes,
+  // then entries of two
+  asm volatile(
+      "s_getpc_b64 s[90:91]\n\t"
+      "s_add_u32 s90, s90, %0\n\t"
+      "s_addc_u32 s91, s91, 0\n\t"
+      "s_setpc_b64 s[90:91]\n\t"
+      ".set .Lcount%=, 0\n\t"
+      ".rept 57\n\t"
+      "s_waitcnt vmcnt(.Lcount%=)\n\t"
+      "s_branch .Lwaited%=\n\t"
+      ".set .Lcount%=, .Lcount%=+1\n\t"
+      ".endr\n"
+      ".Lwaited%=:"
+      :
+      : "s"(to)
+      : "s90", "s91", "scc", "memory");
+}
+
+// Loader i's share of the X chunks: rows 8 (i NB + j) + lane / 8, j < n.
+// Rows are copied in eights up to the last one that N needs (rows past N in
+// the last eight repeat row N - 1); stage rows past those are never written,
+// and whatever they hold only reaches accumulator columns past N.
 template <int NB>
 struct XShare {
   const uint16_t* p[NB];
+  int n;
   __device__ __forceinline__ XShare(const uint16_t* X, int N, long long ld, int i, int lane) {
+    n = __builtin_amdgcn_readfirstlane(min(NB, max(0, (N + 7) / 8 - i * NB)));
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
       const int r = 8 * (i * NB + j) + lane / 8;
       p[j] = X + (size_t)min(r, N - 1) * ld + ((lane % 8) ^ piece_swz(r)) * 8;
     }
   }
-  __device__ __forceinline__ void dma(int kc, int i, uint8_t* dst) const {
+  int col = 0;
+  __device__ __forceinline__ void set(int kc) { col = kc * 64; }
+  // copies the chunk it points at and moves on to the next
+  __device__ __forceinline__ void dma(int i, uint8_t* dst) {
 #pragma unroll
     for (int j = 0; j < NB; ++j)
-      __builtin_amdgcn_global_load_lds(OOO_GLB(p[j] + kc * 64), OOO_LDS(dst + (i * NB + j) * 1024), 16, 0, 0);
+      if (j < n)
+        __builtin_amdgcn_global_load_lds(OOO_GLB(p[j] + col), OOO_LDS(dst + (i * NB + j) * 1024), 16, 0, 0);
+    col += 64;
   }
 };
 
-// Loader wave i over T tiles of `chunks` chunks.  cut(t) is the first group
-// of tile t (cut(T) ends the last); slot_dma(g, kc, dst) copies chunk kc of
-// group g's 32 rows.  The wait for a chunk counts the instructions of the
-// chunks behind it; around a tile boundary where the number of slots of this
-// loader changes it takes the smaller count (waits for a little more).
-template <int NB, int RG, class Cut, class SlotDma>
-__device__ __forceinline__ void for_tiles_load(int T, int chunks, int i, Cut&& cut, SlotDma&& slot_dma,
-                                               const XShare<NB>& xs, uint8_t* lds) {
-  using R = TallRing<NB, RG>;
-  const auto slots_of = [&](int t) { return max(0, min(RG, (cut(t + 1) - cut(t) - i + 3) / 4)); };
-  const int total = T * chunks;
-  int it = 0, ikc = 0, ig = cut(0), in = slots_of(0), istage = 0;  // next chunk to issue
-  const auto issue = [&]() {
-    uint8_t* st = lds + istage * R::STAGE;
-    xs.dma(ikc, i, st + R::WS);
+struct GroupRange {
+  int lo, hi;
+};
+
+// Slots of a tile of ng groups that belong to loader (or compute wave) i.
+template <int RG>
+__device__ __forceinline__ int slots_of(int ng, int i) {
+  return __builtin_amdgcn_readfirstlane(max(0, min(RG, (ng - i + 3) / 4)));
+}
+
+// Loader wave i over `total` chunks from chunk kc0 of tile t0 on; a tile has
+// `chunks` chunks and is the groups tile(t).  slots: the W
+// sources; slots.set(r, g, kc) points source r at chunk kc of group g,
+// slots.dma(r, dst) copies the chunk it points at (4 instructions) and moves
+// on to the next.  The wait for a chunk counts the instructions of the
+// chunks requested behind it; around a tile boundary where this loader's
+// slots change it takes the smaller count (waits for a little more).
+// ng_least: the fewest groups of any tile (tiles shorter than the ring,
+// where a wait can span several).
+template <int NB, int RG, class Tile, class Slots>
+__device__ __forceinline__ void tall_load(int t0, int kc0, int total, int chunks, int ng_least, int i, Tile&& tile,
+                                          Slots&& slots, XShare<NB>& xs, const Ring& ring, uint8_t* lds) {
+  int it = t0, in = 0, ikc = 0, left = total;  // tile and chunk of the next request
+  const auto enter = [&](int t, int kc) {
+    const int g0 = tile(t).lo;
+    in = slots_of<RG>(tile(t).hi - g0, i);
+    ikc = kc;
+    xs.set(kc);
 #pragma unroll
     for (int r = 0; r < RG; ++r)
-      if (r < in) slot_dma(ig + i + 4 * r, ikc, st + (i + 4 * r) * 4096);
-    if (++istage == R::NS) istage = 0;
-    if (++ikc == chunks) {
-      ikc = 0;
-      if (++it < T) {
-        ig = cut(it);
-        in = slots_of(it);
-      }
-    }
+      if (r < in) slots.set(r, g0 + i + 4 * r, kc);
   };
-  for (int q = 0; q < R::NS - 1 && q < total; ++q) issue();
-  // With tiles shorter than the ring a wait can span several tiles: then
-  // take the smallest count of any tile.
-  int least = RG;
-  for (int t = 0; t < T; ++t) least = min(least, slots_of(t));
-  int ckc = 0, ct = 0, cn = slots_of(0);  // chunk being waited for
+  uint8_t* dst = lds;
+  uint8_t* const end = lds + ring.ns * ring.bytes;
+  const auto issue = [&]() {
+    xs.dma(i, dst + ring.xoff);
+#pragma unroll
+    for (int r = 0; r < RG; ++r)
+      if (r < in) slots.dma(r, dst + (i + 4 * r) * 4096);
+    dst += ring.bytes;
+    if (dst == end) dst = lds;
+    if (--left > 0 && ++ikc == chunks) enter(++it, 0);
+  };
+  enter(t0, kc0);
+  int ckc = kc0, ct = t0, cn = in;  // chunk being waited for
+  for (int q = 0; q < ring.ns - 1 && left > 0; ++q) issue();
+  const int least = slots_of<RG>(ng_least, i);
+  const bool long_tiles = chunks >= ring.ns;
   for (int q = 0; q < total; ++q) {
-    const int ahead = min(R::NS - 2, total - 1 - q);
-    const int n = chunks >= R::NS ? min(cn, in) : least;
-    if (n >= 2 && RG >= 2) wait_chunks<4 * (RG >= 2 ? 2 : 1) + NB, R::NS - 2>(ahead);
-    else if (n == 1) wait_chunks<4 + NB, R::NS - 2>(ahead);
-    else wait_chunks<NB, R::NS - 2>(ahead);
+    const int ahead = min(ring.ns - 2, total - 1 - q);
+    wait_vmcnt_at(ahead * (xs.n + 4 * (long_tiles ? min(cn, in) : least)));
     wg_barrier();
-    if (q + R::NS - 1 < total) issue();
-    if (++ckc == chunks) {
+    if (left > 0) issue();
+    if (++ckc == chunks && q + 1 < total) {
       ckc = 0;
-      if (++ct < T) cn = slots_of(ct);
+      ++ct;
+      cn = slots_of<RG>(tile(ct).hi - tile(ct).lo, i);
     }
   }
 }
+
+// W sources of a loader: 32-row groups of the packed or the row layout.
+template <int RG, bool PACKED>
+struct GroupSlots {
+  const uint16_t* W;
+  int chunks, rows, lane;
+  long long ld;
+  const uint16_t* p[RG];
+  int g[RG], kc[RG];
+  __device__ __forceinline__ GroupSlots(const uint16_t* w, int c, int nrows, long long l, int ln)
+      : W(w), chunks(c), rows(nrows), lane(ln), ld(l) {}
+  __device__ __forceinline__ void set(int r, int grp, int k) {
+    if (PACKED) {
+      p[r] = W + ((size_t)(grp / 4) * chunks + k) * (kStreamRows * 64) + 32 * 64 * (grp % 4);
+    } else {
+      g[r] = grp;
+      kc[r] = k;
+    }
+  }
+  __device__ __forceinline__ void dma(int r, uint8_t* dst) {
+    if (PACKED) {
+      dma_w_slot_packed(p[r] + lane * 8, dst);
+      p[r] += kStreamRows * 64;
+    } else {
+      dma_w_slot_rows(W, ld, 32 * g[r], rows, kc[r]++, dst, lane);
+    }
+  }
+};
 
 // `chunks` chunks of compute wave w's slots w + 4 r, r < RA: acc[r][nb] +=
 // slot times node block nb.  Fragments are read one k-step (16 columns)
@@ -235,18 +248,17 @@ __device__ __forceinline__ void for_tiles_load(int T, int chunks, int i, Cut&& c
 // stage of the first chunk (of the block's first tile) is waited for by the
 // caller; `last` leaves out the barrier after the last chunk.
 template <int NB, int RG, int RA>
-__device__ __forceinline__ void tall_run(int chunks, bool last, int w, const uint8_t* lds, const uint32_t (&off)[4],
-                                         int& stage, f32x16 (&acc)[RG][NB]) {
-  using R = TallRing<NB, RG>;
+__device__ __forceinline__ void tall_run(int chunks, bool last, int w, const uint8_t* lds, const Ring& ring,
+                                         const uint32_t (&off)[4], int& stage, f32x16 (&acc)[RG][NB]) {
   bf16x8 af[2][RA], bf[2][NB];
-  const uint8_t* st = lds + stage * R::STAGE;
+  const uint8_t* st = lds + stage * ring.bytes;
   const auto read = [&](int s4, int buf) {
 #pragma unroll
     for (int r = 0; r < RA; ++r)
       af[buf][r] = as_bf16x8(*reinterpret_cast<const u32x4*>(st + (w + 4 * r) * 4096 + off[s4]));
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
-      bf[buf][nb] = as_bf16x8(*reinterpret_cast<const u32x4*>(st + R::WS + nb * 4096 + off[s4]));
+      bf[buf][nb] = as_bf16x8(*reinterpret_cast<const u32x4*>(st + ring.xoff + nb * 4096 + off[s4]));
   };
   const auto mma = [&](int buf) {
 #pragma unroll
@@ -262,8 +274,8 @@ __device__ __forceinline__ void tall_run(int chunks, bool last, int w, const uin
       mma(s4 & 1);
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (++stage == R::NS) stage = 0;
-    st = lds + stage * R::STAGE;
+    if (++stage == ring.ns) stage = 0;
+    st = lds + stage * ring.bytes;
     const bool more = kc + 1 < chunks;
     if (more || !last) lds_read_barrier();
     if (more) read(0, 0);
@@ -275,17 +287,17 @@ __device__ __forceinline__ void tall_run(int chunks, bool last, int w, const uin
 // One tile of ng groups for compute wave w.
 template <int NB, int RG>
 __device__ __forceinline__ void tall_tile(int chunks, bool last, int ng, int w, const uint8_t* lds,
-                                          const uint32_t (&off)[4], int& stage, f32x16 (&acc)[RG][NB]) {
-  using R = TallRing<NB, RG>;
+                                          const Ring& ring, const uint32_t (&off)[4], int& stage,
+                                          f32x16 (&acc)[RG][NB]) {
   if (w >= ng) {  // no slot of this tile: barriers only
     for (int kc = 0; kc < chunks; ++kc) {
-      if (++stage == R::NS) stage = 0;
+      if (++stage == ring.ns) stage = 0;
       if (kc + 1 < chunks || !last) lds_read_barrier();
     }
   } else if (RG == 1 || w + 4 >= ng) {
-    tall_run<NB, RG, 1>(chunks, last, w, lds, off, stage, acc);
+    tall_run<NB, RG, 1>(chunks, last, w, lds, ring, off, stage, acc);
   } else {
-    tall_run<NB, RG, RG>(chunks, last, w, lds, off, stage, acc);
+    tall_run<NB, RG, RG>(chunks, last, w, lds, ring, off, stage, acc);
   }
 }
 

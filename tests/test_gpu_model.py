@@ -97,6 +97,31 @@ def test_linear(N, K, O, packed):
     torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("N,K,I", [
+    (3, 64, 128),        # fewer units than compute units, one chunk
+    (9, 64, 20736),      # more than four units a block: tall tiles, one chunk each, several a block
+    (41, 128, 33024),    # 8 and 9 units a block: two tall tiles of unequal size
+    (100, 192, 20608),   # four node blocks, tall tiles
+    (200, 128, 20608),   # eight node blocks: tiles of four units, two a block
+    (17, 2048, 256),     # few units under a long K: stream-K
+    (130, 4096, 384),    # the same with eight node blocks
+])
+@pytest.mark.parametrize("packed", [True, False], ids=["packed", "rows"])
+def test_linear_swiglu_paths(N, K, I, packed):
+    """The gate/up projection by whole columns per block and through
+    stream-K: against the reference, and no output outside [N][I] written."""
+    print(f"case linear swiglu N={N} K={K} I={I} packed={packed}", flush=True)
+    rs = np.random.default_rng(N + K + I)
+    x, w = _bits(rs, (N, K)), _bits(rs, (2 * I, K), 1.0 / math.sqrt(K))
+    xd, wd = _dev_bf16(x), _dev_bf16(w)
+    ws = torch.zeros(ooo.linear_workspace(N, K, 2 * I), dtype=torch.uint8, device=DEV)
+    act = torch.full((N + 1, I), 7.0, dtype=torch.bfloat16, device=DEV)
+    ooo.linear(xd, ooo.linear_pack(wd) if packed else wd, act, ooo.EPI_SWIGLU_BF16, ws)
+    ref = f64(x) @ f64(w).T
+    assert gh.row_rel_err(_host_f64(act[:N]), om.silu(ref[:, :I]) * ref[:, I:]) <= TOL
+    assert (act[N] == 7.0).all()
+
+
 @pytest.mark.parametrize("scale", [3e4, 0.0])
 def test_linear_partials_beyond_fp16_range(scale):
     """The stream-K partial sums pass through the workspace in fp16 with a
