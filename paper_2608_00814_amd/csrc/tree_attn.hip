@@ -46,6 +46,7 @@ namespace ooo {
 namespace {
 
 constexpr int kTile = 64;         // keys per tile
+constexpr int kEarlyTiles = 16;   // longest runs whose second tile is requested up front
 constexpr int kMaxMaskWords = 16;  // ancestor-mask words per node (up to 1024 nodes)
 
 struct AttnArgs {
@@ -63,12 +64,30 @@ struct AttnArgs {
   float* part_ml;    // per partial row: log2 of the split's weight, exponent of its scale
   int splits, row_blocks, Mpad, tiles_prefix, tiles_total;
   int tps;           // key tiles per split (split s takes tiles [s tps, (s + 1) tps))
+  uint32_t g_inv;    // ceil(2^32 / G) (0 for G = 1): row / G is one multiplication
   const int* P_dev;  // null, or the prefix length in device memory (P bounds it)
 };
 
 // swap bits 2 and 3: the K row a lane loads so that S^T lands with eight
 // consecutive keys per lane and k-step
 __device__ __forceinline__ int sigma(int c) { return (c & ~0xC) | ((c & 4) << 1) | ((c & 8) >> 1); }
+
+// row / G by one multiplication with g_inv = ceil(2^32 / G) (0 for G = 1),
+// which is at most one too large for any row below 2^31
+__device__ __forceinline__ int row_node(int row, int G, uint32_t g_inv) {
+  if (!g_inv) return row;
+  const int n = (int)__umulhi((uint32_t)row, g_inv);
+  return n - (n * G > row);
+}
+
+// Work item of block b when the blocks that share b % 8 (one XCD) take one
+// contiguous range of the items each; the first total % 8 ranges are one
+// longer.  (Only multiples of 8 were ordered so before: 252 blocks, 256 nodes
+// x 14 heads at a 4k prefix, took 22.2 us where 224 blocks took 18.4.)
+__device__ __forceinline__ int xcd_order(int b, int total) {
+  const int x = b & 7;
+  return x * (total >> 3) + min(x, total & 7) + (b >> 3);
+}
 
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 // Kernel-local lambdas must be inlined: an outlined call would take its
@@ -177,8 +196,7 @@ __global__ __launch_bounds__(64 * RG * (SPLIT ? 2 : 1)) void tree_attn_bf16_kern
   uint8_t* const vst[R::NS] = {v0, v1, v2, v3};
 
   const int total = a.Hkv * a.row_blocks * a.splits;
-  int w = blockIdx.x;
-  if (total % 8 == 0) w = (w % 8) * (total / 8) + w / 8;
+  int w = xcd_order(blockIdx.x, total);
   const int s = w % a.splits;
   w /= a.splits;
   const int rb = w % a.row_blocks;
@@ -199,6 +217,7 @@ __global__ __launch_bounds__(64 * RG * (SPLIT ? 2 : 1)) void tree_attn_bf16_kern
   const int t_begin = s * tps;
   const int t_end = min(t_begin + tps, tiles_total);
   const int ntiles = t_end - t_begin;
+  const bool early = ntiles > 1 && tps <= kEarlyTiles;  // key-split kernel: tile 1 requested together with tile 0
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint32_t wave_u = __builtin_amdgcn_readfirstlane(wave);
@@ -208,7 +227,7 @@ __global__ __launch_bounds__(64 * RG * (SPLIT ? 2 : 1)) void tree_attn_bf16_kern
   const int row = rb * BM + rg * 32 + c;
   const bool row_ok = row < a.M;
   const int rr = row_ok ? row : a.M - 1;
-  const int node = rr / a.G;
+  const int node = row_node(rr, a.G, a.g_inv);
   const int head = g * a.G + (rr - node * a.G);
   const uint16_t* const kg = a.k + (size_t)g * a.cap * D;
   const uint16_t* const vg = a.v + (size_t)g * a.cap * D;
@@ -257,7 +276,7 @@ __global__ __launch_bounds__(64 * RG * (SPLIT ? 2 : 1)) void tree_attn_bf16_kern
     const int r = (i * NW + wave) * R::RPI + lane / R::CH;
     dvoff[i] = r * R::ROWB + R::swz(r, lane % R::CH) * 16;
   }
-  auto issue = [&](int t, auto stage_c) OOO_INLINE {
+  auto issue_kv = [&](int t, auto stage_c, bool do_k, bool do_v) OOO_INLINE {
     constexpr int ST = decltype(stage_c)::value;
     int row0, limit;
     tile_rows(t, row0, limit);
@@ -265,10 +284,12 @@ __global__ __launch_bounds__(64 * RG * (SPLIT ? 2 : 1)) void tree_attn_bf16_kern
     const uint16_t* vb = vg + (size_t)row0 * D;
     const uint32_t kl = lds_addr(kst[ST]) + wave_u * 1024, vl = lds_addr(vst[ST]) + wave_u * 1024;
     if (row0 + kTile <= limit) {
+      if (do_k)
 #pragma unroll
-      for (int i = 0; i < PM; ++i) dma16_nt(kb, dvoff[i], kl + i * NW * 1024);
+        for (int i = 0; i < PM; ++i) dma16_nt(kb, dvoff[i], kl + i * NW * 1024);
+      if (do_v)
 #pragma unroll
-      for (int i = 0; i < PM; ++i) dma16_nt(vb, dvoff[i], vl + i * NW * 1024);
+        for (int i = 0; i < PM; ++i) dma16_nt(vb, dvoff[i], vl + i * NW * 1024);
     } else {
       uint32_t vo[PM];
 #pragma unroll
@@ -277,12 +298,15 @@ __global__ __launch_bounds__(64 * RG * (SPLIT ? 2 : 1)) void tree_attn_bf16_kern
         const int rc = min(r, limit - 1 - row0);
         vo[i] = rc * R::ROWB + R::swz(r, lane % R::CH) * 16;
       }
+      if (do_k)
 #pragma unroll
-      for (int i = 0; i < PM; ++i) dma16_nt(kb, vo[i], kl + i * NW * 1024);
+        for (int i = 0; i < PM; ++i) dma16_nt(kb, vo[i], kl + i * NW * 1024);
+      if (do_v)
 #pragma unroll
-      for (int i = 0; i < PM; ++i) dma16_nt(vb, vo[i], vl + i * NW * 1024);
+        for (int i = 0; i < PM; ++i) dma16_nt(vb, vo[i], vl + i * NW * 1024);
     }
   };
+  auto issue = [&](int t, auto stage_c) OOO_INLINE { issue_kv(t, stage_c, true, true); };
   // Every tile issues its PM K instructions before its PM V instructions,
   // so waiting until PM are pending leaves only the tile's V in flight.
 
@@ -298,14 +322,17 @@ __global__ __launch_bounds__(64 * RG * (SPLIT ? 2 : 1)) void tree_attn_bf16_kern
     // ring stage 3 (rows 0..63 in k3, 64..127 in v3): tile 3 is not
     // requested before every wave has read its fragments.  Mask words go
     // to mwords as [row][W] (dword DMA, 64 dwords per instruction).
+    // K of the first tile is requested before them (their addresses take a
+    // while to form) and its V after them.
+    issue_kv(t_begin, std::integral_constant<int, 0>{}, true, false);
     const auto row_src = [&](int r) OOO_INLINE {
       const int rq = min(rb * BM + r, a.M - 1);
-      return rq / a.G;
+      return row_node(rq, a.G, a.g_inv);
     };
     for (int j = wave_u; j < BM / R::RPI; j += NW) {
       const int r = j * R::RPI + lane / R::CH;
       const int rq = min(rb * BM + r, a.M - 1);
-      const int nd = rq / a.G;
+      const int nd = row_node(rq, a.G, a.g_inv);
       const uint32_t off = (uint32_t)((nd * a.Hq + g * a.G + (rq - nd * a.G)) * D) * 2u +
                            (uint32_t)R::swz(r, lane % R::CH) * 16u;
       const uint32_t dst = j * R::RPI < 64 ? lds_addr(k3) + j * 1024 : lds_addr(v3) + (j - 64 / R::RPI) * 1024;
@@ -320,8 +347,17 @@ __global__ __launch_bounds__(64 * RG * (SPLIT ? 2 : 1)) void tree_attn_bf16_kern
   }
 
   // Only the first tile is requested up front: when every block asks for
-  // several tiles at once, each block's first tile lands late.
-  issue(t_begin, std::integral_constant<int, 0>{});
+  // several tiles at once, each block's first tile lands late.  The
+  // key-split kernel over a short run of tiles asks for the second one too,
+  // with K of the first ahead of the queries: 12.6 -> 12.3 us per call at 1
+  // node and a 4k prefix (3 tiles a split), 14.4 -> 14.2 at 64 nodes (6),
+  // but 43.7 -> 44.3 at 256 nodes and 16k (33 tiles).
+  if constexpr (SPLIT) {
+    issue_kv(t_begin, std::integral_constant<int, 0>{}, false, true);
+    if (early) issue(t_begin + 1, std::integral_constant<int, 1>{});
+  } else {
+    issue(t_begin, std::integral_constant<int, 0>{});
+  }
 
   // Per-lane LDS byte offsets (loop invariant).  K fragment (half kh,
   // k-step dk): logical chunk 2dk+u of row sigma(c) + 32kh (the physical
@@ -476,17 +512,16 @@ __global__ __launch_bounds__(64 * RG * (SPLIT ? 2 : 1)) void tree_attn_bf16_kern
     using I2 = std::integral_constant<int, 2>;
     using I3 = std::integral_constant<int, 3>;
     // Tile 0 landed (the compiler does not track the DMA, so the barrier
-    // alone would not wait for it); the mask words in LDS are visible.  Tile
-    // 1 is requested only now: with every block asking for tiles 0 and 1 at
-    // once, each block's tile 0 lands later (15.57 -> 15.41 us per call at
-    // the Qwen3-8B shape, graphs of 36 calls).
+    // alone would not wait for it); the mask words in LDS are visible.  Over
+    // a long run of tiles tile 1 is requested only now.
     // Only K of tile 0 (and Q, the mask words) must have landed: V of tile
     // 0 is first read after barrier 1, whose wait covers it (with a single
     // tile it is read before any other wait, so then wait for it too).
-    if (ntiles > 1) wait_vmcnt<PM>();
+    if (early) wait_vmcnt<PM + PER>();
+    else if (ntiles > 1) wait_vmcnt<PM>();
     else wait_vmcnt<0>();
     __syncthreads();
-    if (ntiles > 1) issue(t_begin + 1, I1{});
+    if (ntiles > 1 && !early) issue(t_begin + 1, I1{});
     {
       const int rq = rg * 32 + c;
       const uint8_t* qs = (rg < 2 ? k3 : v3) + (rq % 64) * R::ROWB;
@@ -778,8 +813,7 @@ __global__ __launch_bounds__(64 * kCombineWaves) void tree_attn_combine_kernel(A
   // Same XCD-aware order as the main kernel: the blocks that share
   // blockIdx % 8 take one contiguous range of (KV head, row block), the
   // range whose partials that XCD wrote, so the loads hit its L2.
-  int b = blockIdx.x;
-  if (gridDim.x % 8 == 0) b = (b % 8) * (gridDim.x / 8) + b / 8;
+  const int b = xcd_order(blockIdx.x, gridDim.x);
   const int wv = b * kCombineWaves + (threadIdx.x >> 6);
   const int nblk = a.Mpad / 32;
   if (wv >= a.Hkv * nblk * NP) return;
@@ -818,7 +852,7 @@ __global__ __launch_bounds__(64 * kCombineWaves) void tree_attn_combine_kernel(A
     }
   }
   const float inv = 1.f / den;
-  const int node = r / a.G, head = g * a.G + r % a.G;
+  const int node = row_node(r, a.G, a.g_inv), head = g * a.G + (r - node * a.G);
   uint16_t* orow = a.out + ((size_t)node * a.Hq + head) * D + 32 * (k / 2) + 16 * (k % 2) + 4 * u;
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
@@ -961,18 +995,21 @@ Plan make_plan(int N, int Hq, int Hkv, int D, int P, ooo_dtype dt, int force_spl
   p.tiles_prefix = (P + kTile - 1) / kTile;
   p.tiles_total = p.tiles_prefix + (N + kTile - 1) / kTile;
   // Split count: as many workgroups as fit on the CUs at once, balancing the
-  // tiles of the busiest split against the partials every split adds (an
-  // empirical cost of about 1.3 us per 64-key tile and 0.5 us per split of
-  // 128-row blocks, half that for 64-row blocks, whose partials are half
-  // the size: at 32 nodes, 2 query heads per KV head and a 1k prefix, 9
-  // splits take 9.96 us per call and the 6 of the 128-row cost 10.8 us).
-  // Units of 0.05 us.
+  // tiles of the busiest split against the merge of the partials: a tile
+  // costs about 1 us, a split 0.1 us (0.15 us where the blocks themselves are
+  // cheap: 64 rows of 64) and the merge, a second launch, 0.5 us more than the
+  // work it takes off the blocks, 1 us for few rows (units of 0.05 us; fitted to graphs of calls over 196 shapes: 1 to 256
+  // nodes, prefixes 40 to 16384, 1 to 8 KV heads, head_dim 64 and 128, and
+  // every split count).  The earlier 1.3 us per tile and 0.25 to 0.5 us per
+  // split chose too few splits where the blocks do not fill the chip: 100
+  // nodes x 8 heads of 64 at prefix 1024 took 9.6 us with 6 splits and
+  // 7.9 us with 18.
   const int base = Hkv * p.row_blocks;
   const int max_splits = device_cus() / base > 1 ? device_cus() / base : 1;
-  const int split_cost = p.waves == 2 ? 5 : 10;
+  const int split_cost = D == 64 && p.waves == 2 ? 3 : 2, merge_cost = M <= 32 ? 20 : 10;
   int splits = 1, best = INT32_MAX;
   for (int sc = 1; sc <= max_splits && sc <= p.tiles_total; ++sc) {
-    const int cost = 26 * ((p.tiles_total + sc - 1) / sc) + split_cost * sc;
+    const int cost = 20 * ((p.tiles_total + sc - 1) / sc) + split_cost * sc + (sc > 1 ? merge_cost : 0);
     if (cost < best) best = cost, splits = sc;
   }
   if (force_splits > 0) splits = force_splits;
@@ -1067,6 +1104,7 @@ extern "C" int ooo_tree_attn_ex(const void* q, const void* k_cache, const void* 
     a.tiles_prefix = p.tiles_prefix;
     a.tiles_total = p.tiles_total;
     a.tps = p.tps;
+    a.g_inv = G > 1 ? (uint32_t)(((1ull << 32) + G - 1) / G) : 0u;
     if (p.splits > 1) {
       a.part_o = (uint32_t*)workspace;
       a.part_ml = (float*)((uint8_t*)workspace + (size_t)p.splits * n_kv_heads * p.Mpad * head_dim * 2);

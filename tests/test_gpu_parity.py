@@ -228,6 +228,32 @@ def test_attention_split_starting_at_a_boundary_tile(case):
     assert gh.row_rel_err(got, ref) <= gh.ATTN_TOL
 
 
+# (P, N, G, Hkv, D, splits): the edges of the planner's and the kernel's rules
+PLAN_EDGES = [
+    (40, 8, 4, 2, 128, 0),     # 2 tiles, 32 rows: one split, no merge
+    (40, 9, 4, 2, 128, 0),     # ... 36 rows: two splits
+    (40, 20, 1, 2, 64, 0),
+    (960, 64, 4, 1, 128, 1),   # runs of 16 tiles: the second tile requested up front
+    (1000, 64, 4, 1, 128, 1),  # ... of 17: after the first has landed
+    (1984, 40, 7, 3, 128, 5),  # 3 row blocks x 3 heads x 5 splits: a grid that is no multiple of 8; rows / 7
+    (500, 33, 13, 1, 64, 3),   # 4 row blocks x 3 splits; rows / 13
+    (300, 3, 1000, 1, 128, 2),  # more query heads a KV head than rows in a block
+]
+
+
+@pytest.mark.parametrize("case", PLAN_EDGES, ids=[f"P{c[0]}-N{c[1]}-G{c[2]}-Hkv{c[3]}-D{c[4]}-S{c[5]}"
+                                                  for c in PLAN_EDGES])
+def test_attention_plan_edges(case):
+    P, N, G, Hkv, D, splits = case
+    print(f"case attention plan edge {case}", flush=True)
+    rs, q, k, v, cap = _attn_inputs(P, N, G, Hkv, D, "bf16", seed=P * N + G)
+    t = _trie("random", N, rs)
+    mask = ov.ancestor_masks(t["parent"], 1)
+    got = _run_attn(q, k, v, P, N, mask, G * Hkv, Hkv, D, "bf16", force_splits=splits)
+    ref = ov.tree_attention(wl.to_f64(q, "bf16"), wl.to_f64(k, "bf16"), wl.to_f64(v, "bf16"), P, t["parent"], Hkv)
+    assert gh.row_rel_err(got, ref) <= gh.ATTN_TOL
+
+
 def test_attention_workspace_reuse_across_shapes():
     """One workspace serves calls of different shapes, head sizes and split
     counts in a row: nothing a call reads from it is left over from another
