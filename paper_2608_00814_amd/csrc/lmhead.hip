@@ -172,32 +172,116 @@ __global__ __launch_bounds__(256) void lmhead_pack_kernel(const uint16_t* __rest
   st16(out + i * 8, v);
 }
 
-// float32 path: one thread per vocabulary row, one block column per node.
+// float32 path, on the f32 matrix instruction (16x16x4): a block takes tiles
+// of 16 vocabulary rows against 16*NB nodes, its four waves a quarter of H
+// each; the waves' partial products meet in LDS and wave nb turns those of
+// node block nb into logits and running winners.  Operands go straight from
+// memory to registers, 16 bytes per lane (four lanes cover 64 bytes of a
+// row), 64 columns ahead of their use; lane (c, q) of step s holds columns
+// 16 s + 4 q .. +3; the order of the columns inside a step is the same for
+// both operands.  Bound by latency at small sizes and by reads of X from the
+// L2 at large ones.  One thread per vocabulary row and a block column per
+// node, the earlier form, read W once per node: per call 64 nodes x H 1024 x V
+// 8000 took 325 us and now take 33, 100 x 1024 x 32000 12.9 ms and 177 us, 25 x
+// 256 x 1024 13.2 and 7.6 us, 40 x 64 x 500 7.5 and 7.4.
+template <int NB>
 __global__ __launch_bounds__(256) void lmhead_f32_kernel(const float* __restrict__ X, const float* __restrict__ Wt,
                                                          int N, int H, int V, Cand* __restrict__ partial,
                                                          float* __restrict__ logits) {
-  __shared__ Cand red[256];
-  const int n = blockIdx.y;
-  const int r = blockIdx.x * 256 + threadIdx.x;
-  float acc = -INFINITY;
-  if (r < V) {
-    const f32x4* w4 = reinterpret_cast<const f32x4*>(Wt + (size_t)r * H);
-    const f32x4* x4 = reinterpret_cast<const f32x4*>(X + (size_t)n * H);
-    f32x4 s = {0.f, 0.f, 0.f, 0.f};
-    for (int k = 0; k < H / 4; ++k) s += w4[k] * x4[k];
-    acc = (s[0] + s[1]) + (s[2] + s[3]);
-    if (logits) logits[(size_t)n * V + r] = acc;
-  }
-  red[threadIdx.x] = Cand{acc, r < V ? r : 0x7FFFFFFF};
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if (threadIdx.x < off) {
-      const Cand o = red[threadIdx.x + off];
-      if (better(o.v, o.i, red[threadIdx.x].v, red[threadIdx.x].i)) red[threadIdx.x] = o;
+  constexpr int U = 4;  // 16-column steps per round of loads
+  __shared__ f32x4 red[4][NB][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c = lane & 15, qd = lane >> 4;
+  const int n0 = blockIdx.y * 16 * NB;
+  const int kq = (H + 63) / 64 * 16;  // columns per wave
+  const int k_begin = min(wave * kq, H), k_end = min(k_begin + kq, H);
+  const int tiles = (V + 15) / 16;
+  const float* xr[NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) xr[nb] = X + (size_t)min(n0 + 16 * nb + c, N - 1) * H;
+  const int n = n0 + 16 * wave + c;  // the node of the lane's logits
+  const bool vec = V % 4 == 0 && (reinterpret_cast<uintptr_t>(logits) & 15) == 0;
+  Cand best{-INFINITY, 0x7FFFFFFF};
+  const float* wr = Wt + (size_t)min(16 * (int)blockIdx.x + c, V - 1) * H;
+  f32x4 wv[2][U], xv[2][NB][U], acc[NB][2];
+  auto load = [&](int b, int k0) {  // steps past the wave's range are loaded from the row's end and not used
+#pragma unroll
+    for (int s = 0; s < U; ++s) {
+      const int kk = min(k0 + 16 * s + 4 * qd, H - 4);
+      wv[b][s] = *reinterpret_cast<const f32x4*>(wr + kk);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) xv[b][nb][s] = *reinterpret_cast<const f32x4*>(xr[nb] + kk);
     }
+  };
+  auto mul_step = [&](int b, int s) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+        acc[nb][s & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[b][s][j], xv[b][nb][s][j], acc[nb][s & 1], 0, 0, 0);
+  };
+  auto mul_full = [&](int b) {
+#pragma unroll
+    for (int s = 0; s < U; ++s) mul_step(b, s);
+  };
+  auto mul_tail = [&](int b, int k0) {
+#pragma unroll
+    for (int s = 0; s < U; ++s) {
+      const int kk = k0 + 16 * s;
+      if (kk >= k_end) break;
+      if (kk + 16 > H && kk + 4 * qd >= H) {  // H no multiple of 16: zeros on both sides
+        wv[b][s] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) xv[b][nb][s] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+      mul_step(b, s);
+    }
+  };
+  load(0, k_begin);
+  for (int t = blockIdx.x; t < tiles; t += gridDim.x) {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) acc[nb][0] = acc[nb][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // The loop's loads are unconditional: under a branch the wait for one
+    // round would be a wait for all that are in flight.
+    int k0 = k_begin;
+    for (; k0 + 32 * U <= k_end; k0 += 32 * U) {
+      load(1, k0 + 16 * U);
+      mul_full(0);
+      load(0, k0 + 32 * U);
+      mul_full(1);
+    }
+    if (k0 < k_end) {
+      if (k0 + 16 * U < k_end) load(1, k0 + 16 * U);
+      mul_tail(0, k0);
+      mul_tail(1, k0 + 16 * U);
+    }
+    wr = Wt + (size_t)min(16 * (t + (int)gridDim.x) + c, V - 1) * H;  // the next tile's first columns
+    load(0, k_begin);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) red[wave][nb][lane] = acc[nb][0] + acc[nb][1];
     __syncthreads();
+    if (wave < NB && n < N) {
+      const f32x4 l = (red[0][wave][lane] + red[1][wave][lane]) + (red[2][wave][lane] + red[3][wave][lane]);
+      const int r0 = 16 * t + 4 * qd;
+      if (logits && vec && r0 < V) {
+        *reinterpret_cast<f32x4*>(logits + (size_t)n * V + r0) = l;
+      } else if (logits) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (r0 + r < V) logits[(size_t)n * V + r0 + r] = l[r];
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (r0 + r < V && better(l[r], r0 + r, best.v, best.i)) best = Cand{l[r], r0 + r};
+    }
+    __syncthreads();  // before the next tile's partials
   }
-  if (threadIdx.x == 0) partial[(size_t)blockIdx.x * N + n] = red[0];
+#pragma unroll
+  for (int off = 16; off < 64; off *= 2) {
+    const Cand o{shfl_xor_f(best.v, off), shfl_xor_i(best.i, off)};
+    if (better(o.v, o.i, best.v, best.i)) best = o;
+  }
+  if (wave < NB && qd == 0 && n < N) partial[(size_t)blockIdx.x * N + n] = best;
 }
 
 // One block per node: best of the per-block winners.
@@ -237,7 +321,9 @@ LmPlan lm_plan(int N, int H, int V, ooo_dtype dt) {
     const int groups = (V + 31) / 32;
     p.blocks = groups < device_cus() ? groups : device_cus();  // persistent grid: one block per CU
   } else {
-    p.blocks = (V + 255) / 256;
+    p.nb = N <= 16 ? 1 : N <= 32 ? 2 : 4;
+    const int tiles = (V + 15) / 16;
+    p.blocks = tiles < 4 * device_cus() ? tiles : 4 * device_cus();  // four blocks of four waves per CU
   }
   p.ws_bytes = (size_t)p.blocks * N * sizeof(Cand);
   return p;
@@ -316,8 +402,12 @@ extern "C" int ooo_lmhead_argmax(const void* hidden, const void* weight, int32_t
     else OOO_LM_LAUNCH(8, 1);
 #undef OOO_LM_LAUNCH
   } else {
-    lmhead_f32_kernel<<<dim3(p.blocks, n_nodes), 256, 0, st>>>((const float*)hidden, (const float*)weight, n_nodes,
-                                                              hidden_dim, vocab, part, logits);
+    const dim3 grid(p.blocks, (n_nodes + 16 * p.nb - 1) / (16 * p.nb));
+    const float* X = (const float*)hidden;
+    const float* W = (const float*)weight;
+    if (p.nb == 1) lmhead_f32_kernel<1><<<grid, 256, 0, st>>>(X, W, n_nodes, hidden_dim, vocab, part, logits);
+    else if (p.nb == 2) lmhead_f32_kernel<2><<<grid, 256, 0, st>>>(X, W, n_nodes, hidden_dim, vocab, part, logits);
+    else lmhead_f32_kernel<4><<<grid, 256, 0, st>>>(X, W, n_nodes, hidden_dim, vocab, part, logits);
   }
   lmhead_finalize_kernel<<<n_nodes, 256, 0, st>>>(part, p.blocks, n_nodes, argmax_ids, max_logit);
   const hipError_t e = hipGetLastError();

@@ -863,85 +863,155 @@ __global__ __launch_bounds__(64 * kCombineWaves) void tree_attn_combine_kernel(A
   }
 }
 
-// float32 path: one workgroup of 256 threads per (node, query head).  Keys
-// go in chunks of 256, one key per thread: key j is cache row j (prefix
-// rows, then node rows P + i, allowed when bit i of the node's ancestor mask
-// is set).  Each thread scores its key against the query (in LDS), the
-// block takes the chunk's max, and the probabilities go to LDS; then thread
-// t accumulates column t % D of P V over the keys j = t / D (mod 256 / D),
-// with the running max/sum of an online softmax across chunks.  The
-// 256 / D column partials are added at the end.
+// float32 path: one workgroup per (KV head, block of 16 of its M = N*G query
+// rows), on the f32 matrix instruction (16x16x4).  The keys go in tiles of 16
+// (prefix tiles, then tree tiles), dealt round-robin to the waves; a wave
+// computes S^T = K Q^T and O^T += V^T P^T with its own online softmax and the
+// waves merge through LDS at the end.  No operand is staged: K and V are read
+// in 64- and 256-byte runs straight into operand registers, and P is already
+// in B-operand order (lane (c, q) holds row c's scores of keys 4q .. 4q+3).
+// Lane (c, q) of the O^T accumulator dt holds row c, columns
+// 64 (dt / 4) + 16 q + 4 r + dt % 4 (the V columns are permuted so that a
+// lane loads 16 bytes).  Bound by the latency of the serial tiles of a wave at
+// small sizes and by the matrix rate at large ones.  A block per
+// (node, query head) with one thread per key, the earlier form, read every
+// key row once per query head in 16-byte pieces of 64 different rows: 64 nodes
+// x 16 heads over 4 KV heads of 128 at prefix 1024 took 153 us and now takes
+// 34, 25 nodes x 4 heads of 64 at 128 10.7 and 7.8, one node at 128 9.7 and 6.5.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // dword-aligned
 template <int D>
-__global__ __launch_bounds__(256) void tree_attn_f32_kernel(const float* q, const float* k, const float* v,
-                                                            long long cap, int P, const int* P_dev, int N,
-                                                            const uint64_t* mask, int W, int Hq, int Hkv,
-                                                            float scale, float* out) {
-  constexpr int NT = 256, PARTS = NT / D;
-  __shared__ float qs[D];
-  __shared__ float ps[NT];
-  __shared__ float red[NT / 64];
-  __shared__ float opart[NT];
+__global__ __launch_bounds__(64 * 1024 / D) void tree_attn_f32_kernel(const float* q, const float* k, const float* v,
+                                                                      long long cap, int P, const int* P_dev, int N,
+                                                                      const uint64_t* mask, int W, int Hq, int Hkv,
+                                                                      float scale, float* out) {
+  constexpr int NW = 1024 / D;  // waves at most: 64 KiB of partial O
+  constexpr int KS = D / 16;    // 16-column steps of a row
+  __shared__ f32x4 o_s[NW][KS][64];
+  __shared__ f32x2_t ml_s[NW][16];
   if (P_dev) P = min(max(*P_dev, 0), P);
-  const int node = blockIdx.x / Hq, head = blockIdx.x % Hq;
-  const int g = head / (Hq / Hkv);
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int G = Hq / Hkv, M = N * G, row_blocks = (M + 15) / 16;
+  const int g = blockIdx.x / row_blocks, rb = blockIdx.x - g * row_blocks;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nw = blockDim.x >> 6;
+  const int c = lane & 15, qd = lane >> 4;
+  const int row = rb * 16 + c, rr = min(row, M - 1), node = rr / G, head = g * G + rr - node * G;
   const float sl2 = scale * 1.4426950408889634f;
-  if (t < D) qs[t] = q[((size_t)node * Hq + head) * D + t] * sl2;
   const float* kb = k + (size_t)g * cap * D;
   const float* vb = v + (size_t)g * cap * D;
-  const uint64_t* mrow = mask + (size_t)node * W;
-  const int col = t % D, part = t / D;
-  float m_run = -INFINITY, l_run = 0.f, o = 0.f;
-  __syncthreads();
-  for (int c0 = 0; c0 < P + N; c0 += NT) {
-    const int j = c0 + t;
-    bool ok = j < P;
-    if (!ok && j < P + N) ok = (mrow[(j - P) >> 6] >> ((j - P) & 63)) & 1ull;
-    float sc = -INFINITY;
-    if (ok) {
-      const float4* kr = reinterpret_cast<const float4*>(kb + (size_t)j * D);
-      float a0 = 0.f, a1 = 0.f;
+  const int tiles_prefix = (P + 15) / 16, tiles = tiles_prefix + (N + 15) / 16;
+
+  f32x4 qv[KS], kv[KS];
 #pragma unroll
-      for (int d4 = 0; d4 < D / 4; d4 += 2) {
-        const float4 x = kr[d4], y = kr[d4 + 1];
-        a0 += x.x * qs[4 * d4] + x.y * qs[4 * d4 + 1] + x.z * qs[4 * d4 + 2] + x.w * qs[4 * d4 + 3];
-        a1 += y.x * qs[4 * d4 + 4] + y.y * qs[4 * d4 + 5] + y.z * qs[4 * d4 + 6] + y.w * qs[4 * d4 + 7];
+  for (int s = 0; s < KS; ++s)
+    qv[s] = *reinterpret_cast<const f32x4u*>(q + ((size_t)node * Hq + head) * D + 16 * s + 4 * qd) * sl2;
+  auto tile_rows = [&](int t, int& row0, int& last) {
+    const bool tree = t >= tiles_prefix;
+    row0 = tree ? P + 16 * (t - tiles_prefix) : 16 * t;
+    last = (tree ? P + N : P) - 1;
+  };
+  auto load_k = [&](int t) {  // rows past the region re-read its last one (masked below)
+    int row0, last;
+    tile_rows(t, row0, last);
+    const float* kr = kb + (size_t)min(row0 + c, last) * D + 4 * qd;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) kv[s] = *reinterpret_cast<const f32x4u*>(kr + 16 * s);
+  };
+  f32x4 o[KS];
+#pragma unroll
+  for (int dt = 0; dt < KS; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m_run = -INFINITY, l_run = 0.f;
+  if (wave < tiles) load_k(wave);
+  // Every load of a tile is unconditional (the mask word, the next tile's K):
+  // under a branch the wait for one would be a wait for all in flight.
+  for (int t = wave; t < tiles; t += nw) {
+    int row0, last;
+    tile_rows(t, row0, last);
+    const int tt = t - tiles_prefix;
+    const uint64_t mword = mask[(size_t)node * W + (max(tt, 0) >> 2)];
+    f32x4 vv[4][D / 64];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int h = 0; h < D / 64; ++h)
+        vv[r][h] = *reinterpret_cast<const f32x4u*>(vb + (size_t)min(row0 + 4 * qd + r, last) * D + 64 * h + 4 * c);
+    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;  // two chains: half the roundings in a row
+#pragma unroll
+    for (int s = 0; s < KS; s += 2)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[s][j], qv[s][j], s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[s + 1][j], qv[s + 1][j], s1, 0, 0, 0);
       }
-      sc = a0 + a1;
-    }
-    float mx = sc;
-    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, shfl_xor_f(mx, off));
-    if (lane == 0) red[wave] = mx;
-    __syncthreads();
-    mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    const float m_new = fmaxf(m_run, mx);  // finite: every node sees itself
-    const float alpha = exp2f(m_run - m_new);
-    const float p = ok ? exp2f(sc - m_new) : 0.f;
-    ps[t] = p;
-    float sum = p;
-    for (int off = 32; off > 0; off >>= 1) sum += shfl_xor_f(sum, off);
-    __syncthreads();  // ps complete; every wave has read red
-    if (lane == 0) red[wave] = sum;
-    __syncthreads();
-    l_run = l_run * alpha + ((red[0] + red[1]) + (red[2] + red[3]));
-    m_run = m_new;
-    float acc = 0.f;
-    const int nk = min(NT, P + N - c0);
-    for (int jj = part; jj < nk; jj += PARTS) {
-      const float pj = ps[jj];
-      if (pj != 0.f) acc += pj * vb[(size_t)(c0 + jj) * D + col];  // rows of keys not allowed are not read
-    }
-    o = o * alpha + acc;
-    __syncthreads();  // before the next chunk overwrites ps and red
-  }
-  opart[t] = o;
-  __syncthreads();
-  if (t < D) {
-    float s = 0.f;
+    load_k(min(t + nw, tiles - 1));
+    const uint64_t mw = tt >= 0 ? mword >> (16 * (tt & 3) + 4 * qd) : ~0ull;
+    float p[4], mx = -INFINITY;
 #pragma unroll
-    for (int pp = 0; pp < PARTS; ++pp) s += opart[pp * D + t];
-    out[((size_t)node * Hq + head) * D + t] = s / l_run;
+    for (int r = 0; r < 4; ++r) {
+      const bool ok = row0 + 4 * qd + r <= last && ((mw >> r) & 1ull);
+      p[r] = ok ? s0[r] + s1[r] : -INFINITY;
+      mx = fmaxf(mx, p[r]);
+    }
+    mx = fmaxf(mx, shfl_xor_f(mx, 16));
+    mx = fmaxf(mx, shfl_xor_f(mx, 32));
+    const float m_new = fmaxf(m_run, mx), base = m_new == -INFINITY ? 0.f : m_new;
+    const float alpha = exp2f(m_run - base);
+    m_run = m_new;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) p[r] = exp2f(p[r] - base);
+    l_run = l_run * alpha + ((p[0] + p[1]) + (p[2] + p[3]));
+#pragma unroll
+    for (int dt = 0; dt < KS; ++dt) o[dt] *= alpha;
+    // A row of V that is not finite counts only for the query rows that see
+    // it: a tree tile that holds one is added key by key instead.
+    bool odd = false;
+    if (tt >= 0) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int h = 0; h < D / 64; ++h)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) odd |= !(__builtin_fabsf(vv[r][h][e]) < INFINITY);
+    }
+    if (__any(odd)) {
+      for (int q4 = 0; q4 < 4; ++q4)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float pk = __shfl(p[r], 16 * q4 + c, kWave);
+          if (pk == 0.f) continue;
+          const float* vr = vb + (size_t)min(row0 + 4 * q4 + r, last) * D + 16 * qd;
+#pragma unroll
+          for (int dt = 0; dt < KS; ++dt)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[dt][e] += pk * vr[64 * (dt >> 2) + 4 * e + (dt & 3)];
+        }
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int dt = 0; dt < KS; ++dt)
+          o[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[r][dt >> 2][dt & 3], p[r], o[dt], 0, 0, 0);
+    }
   }
+  l_run += shfl_xor_f(l_run, 16);
+  l_run += shfl_xor_f(l_run, 32);
+#pragma unroll
+  for (int dt = 0; dt < KS; ++dt) o_s[wave][dt][lane] = o[dt];
+  if (qd == 0) ml_s[wave][c] = f32x2_t{m_run, l_run};
+  __syncthreads();
+  if (wave >= KS || row >= M) return;  // wave dt adds accumulator dt
+  float m = -INFINITY, den = 0.f;
+  for (int w = 0; w < nw; ++w) m = fmaxf(m, ml_s[w][c][0]);
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (int w = 0; w < nw; ++w) {
+    const f32x2_t ml = ml_s[w][c];
+    const float wgt = exp2f(ml[0] - m);  // m is finite: every node sees itself
+    den += wgt * ml[1];
+    acc += wgt * o_s[w][wave][lane];
+  }
+  float* orow = out + ((size_t)node * Hq + head) * D + 64 * (wave >> 2) + 16 * qd + (wave & 3);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) orow[4 * r] = acc[r] / den;
 }
 
 // The combine kernel loads exactly the splits there are (up to 16; more in
@@ -1069,15 +1139,22 @@ extern "C" int ooo_tree_attn_ex(const void* q, const void* k_cache, const void* 
   const int G = n_q_heads / n_kv_heads;
 
   if (dt == OOO_F32) {
-    const dim3 grid(n_nodes * n_q_heads);
+    const dim3 grid(n_kv_heads * (int)(((int64_t)n_nodes * G + 15) / 16));
+    // a wave per key tile, at least the head_dim / 16 that merge and at most
+    // the 1024 / head_dim whose partial sums fit
+    const int tiles = (prefix_len + 15) / 16 + (n_nodes + 15) / 16;
+    const int lo = head_dim / 16, hi = 1024 / head_dim;
+    const int threads = 64 * (tiles < lo ? lo : tiles > hi ? hi : tiles);
     if (head_dim == 64)
-      tree_attn_f32_kernel<64><<<grid, 256, 0, st>>>((const float*)q, (const float*)k_cache, (const float*)v_cache,
-                                                    cap, prefix_len, prefix_len_dev, n_nodes, anc_mask, mask_words,
-                                                    n_q_heads, n_kv_heads, scale, (float*)out);
+      tree_attn_f32_kernel<64><<<grid, threads, 0, st>>>((const float*)q, (const float*)k_cache,
+                                                         (const float*)v_cache, cap, prefix_len, prefix_len_dev,
+                                                         n_nodes, anc_mask, mask_words, n_q_heads, n_kv_heads, scale,
+                                                         (float*)out);
     else
-      tree_attn_f32_kernel<128><<<grid, 256, 0, st>>>((const float*)q, (const float*)k_cache, (const float*)v_cache,
-                                                     cap, prefix_len, prefix_len_dev, n_nodes, anc_mask,
-                                                     mask_words, n_q_heads, n_kv_heads, scale, (float*)out);
+      tree_attn_f32_kernel<128><<<grid, threads, 0, st>>>((const float*)q, (const float*)k_cache,
+                                                          (const float*)v_cache, cap, prefix_len, prefix_len_dev,
+                                                          n_nodes, anc_mask, mask_words, n_q_heads, n_kv_heads, scale,
+                                                          (float*)out);
   } else {
     const Plan p = make_plan(n_nodes, n_q_heads, n_kv_heads, head_dim, prefix_len, dt, force_splits);
     OOO_REQUIRE(ws_bytes >= p.ws_bytes && (p.ws_bytes == 0 || workspace), OOO_ERR_CAPACITY,

@@ -254,6 +254,44 @@ def test_attention_plan_edges(case):
     assert gh.row_rel_err(got, ref) <= gh.ATTN_TOL
 
 
+# (P, N, G, Hkv, D): edges of the float32 kernel's 16-row blocks and 16-key
+# tiles: no prefix, one row, a full tile and one key more, several mask words,
+# more waves than tiles, G that does not divide a block
+F32_ATTN_EDGES = [(0, 1, 1, 1, 64), (0, 17, 3, 2, 64), (1, 1, 1, 1, 128), (16, 16, 1, 1, 128), (17, 65, 5, 2, 64),
+                  (255, 4, 4, 1, 128), (700, 130, 2, 2, 128), (1000, 1, 4, 2, 64)]
+
+
+@pytest.mark.parametrize("case", F32_ATTN_EDGES, ids=[f"P{c[0]}-N{c[1]}-G{c[2]}-Hkv{c[3]}-D{c[4]}"
+                                                      for c in F32_ATTN_EDGES])
+def test_attention_f32_edges(case):
+    P, N, G, Hkv, D = case
+    print(f"case attention f32 edge {case}", flush=True)
+    rs, q, k, v, cap = _attn_inputs(P, N, G, Hkv, D, "f32", seed=P * N + G)
+    t = _trie("chain" if N < 4 else "random", N, rs)
+    mask = ov.ancestor_masks(t["parent"], (N + 63) // 64)
+    got = _run_attn(q, k, v, P, N, mask, G * Hkv, Hkv, D, "f32")
+    ref = ov.tree_attention(wl.to_f64(q, "f32"), wl.to_f64(k, "f32"), wl.to_f64(v, "f32"), P, t["parent"], Hkv)
+    assert gh.row_rel_err(got, ref) <= 1e-5
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_attention_f32_rows_not_seen_may_hold_anything(D):
+    """A tree row that is not finite reaches only the nodes that see it."""
+    print(f"case attention f32 unseen rows D={D}", flush=True)
+    P, N, G, Hkv = 50, 40, 2, 2
+    rs, q, k, v, cap = _attn_inputs(P, N, G, Hkv, D, "f32", seed=3)
+    t = _trie("star", N, rs)
+    mask = ov.ancestor_masks(t["parent"], 1)
+    ref = ov.tree_attention(wl.to_f64(q, "f32"), wl.to_f64(k, "f32"), wl.to_f64(v, "f32"), P, t["parent"], Hkv)
+    k[:, P + 7] = np.nan
+    v[:, P + 7] = np.inf
+    v[0, P + 21, D - 1] = np.nan
+    got = _run_attn(q, k, v, P, N, mask, G * Hkv, Hkv, D, "f32")
+    rest = [i for i in range(N) if i not in (7, 21)]
+    assert gh.row_rel_err(got[rest], ref[rest]) <= 1e-5
+    assert np.isnan(got[7]).any() and np.isnan(got[21, :G, D - 1]).all()
+
+
 def test_attention_workspace_reuse_across_shapes():
     """One workspace serves calls of different shapes, head sizes and split
     counts in a row: nothing a call reads from it is left over from another
@@ -374,6 +412,32 @@ def test_lmhead_edges(case, packed):
     assert clear.sum() >= 0.7 * N
     assert np.array_equal(ids[clear], g["ids"][clear])
     assert np.allclose(mx[clear], g["max_logit"][clear], rtol=1e-3, atol=1e-3)
+
+
+# (N, H, V): edges of the float32 kernel's node blocks (16, 32, 64), column
+# steps (16, split over four waves, rounds of 64 and 128) and row tiles (16,
+# more than there are blocks), and V that leaves no aligned rows of logits
+F32_LM_EDGES = [(1, 4, 1), (16, 20, 15), (17, 64, 17), (33, 68, 1000), (65, 256, 333), (7, 1040, 4001), (2, 516, 20000),
+                (64, 512, 16400)]
+
+
+@pytest.mark.parametrize("case", F32_LM_EDGES, ids=[f"N{c[0]}-H{c[1]}-V{c[2]}" for c in F32_LM_EDGES])
+def test_lmhead_f32_edges(case):
+    N, H, V = case
+    print(f"case lmhead f32 edge {case}", flush=True)
+    rs = np.random.default_rng(N + H + V)
+    x = rs.normal(size=(N, H)).astype(np.float32)
+    w = (rs.normal(size=(V, H)) / math.sqrt(H)).astype(np.float32)
+    if V > 600:  # equal rows in different tiles: the lowest index wins
+        w[V - 1] = w[577] = w[3] = x[0] * np.float32(8.0)
+    ids, mx, lg = _run_lm(x, w, "f32")
+    ref = ov.lm_head_logits(wl.to_f64(x, "f32"), wl.to_f64(w, "f32"))
+    g = ov.greedy_tokens(ref)
+    assert gh.row_rel_err(lg, ref) <= 1e-5
+    assert V <= 600 or ids[0] == 3
+    clear = g["margin"] >= 1e-4
+    assert np.array_equal(ids[clear], g["ids"][clear])
+    assert np.array_equal(mx, lg[np.arange(N), ids].astype(np.float32))
 
 
 @pytest.mark.parametrize("packed", [False, True])
