@@ -877,7 +877,10 @@ __global__ __launch_bounds__(64 * kCombineWaves) void tree_attn_combine_kernel(A
 // (node, query head) with one thread per key, the earlier form, read every
 // key row once per query head in 16-byte pieces of 64 different rows: 64 nodes
 // x 16 heads over 4 KV heads of 128 at prefix 1024 took 153 us and now takes
-// 34, 25 nodes x 4 heads of 64 at 128 10.7 and 7.8, one node at 128 9.7 and 6.5.
+// 33, 25 nodes x 4 heads of 64 at 128 10.7 and 8.0, one node at 128 9.7 and
+// 6.8.  Error against 64 bits at these three: 2.7e-7 -> 1.8e-7, 1.7e-7 ->
+// 1.5e-7, 1.9e-7 -> 1.6e-7 (means over 12 seeds): products are added in chains
+// of eight and the chains in trees.
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // dword-aligned
 template <int D>
 __global__ __launch_bounds__(64 * 1024 / D) void tree_attn_f32_kernel(const float* q, const float* k, const float* v,
@@ -926,41 +929,55 @@ __global__ __launch_bounds__(64 * 1024 / D) void tree_attn_f32_kernel(const floa
   for (int t = wave; t < tiles; t += nw) {
     int row0, last;
     tile_rows(t, row0, last);
+    f32x4 vv[4][D / 64];
     const int tt = t - tiles_prefix;
     const uint64_t mword = mask[(size_t)node * W + (max(tt, 0) >> 2)];
-    f32x4 vv[4][D / 64];
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
       for (int h = 0; h < D / 64; ++h)
         vv[r][h] = *reinterpret_cast<const f32x4u*>(vb + (size_t)min(row0 + 4 * qd + r, last) * D + 64 * h + 4 * c);
-    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;  // two chains: half the roundings in a row
+    // Chains of eight products added in a tree: as few roundings in a row as
+    // sums of four-column products.
+    f32x4 score = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int s = 0; s < KS; s += 2)
+    for (int s = 0; s < KS; s += 4) {
+      f32x4 sc[8];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[s][j], qv[s][j], s0, 0, 0, 0);
-        s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[s + 1][j], qv[s + 1][j], s1, 0, 0, 0);
-      }
+      for (int ch = 0; ch < 8; ++ch) sc[ch] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int ch = 0; ch < 8; ++ch) {
+          const int x = s + ch / 2, e = 2 * (ch & 1) + j;
+          sc[ch] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[x][e], qv[x][e], sc[ch], 0, 0, 0);
+        }
+      score += ((sc[0] + sc[1]) + (sc[2] + sc[3])) + ((sc[4] + sc[5]) + (sc[6] + sc[7]));
+    }
     load_k(min(t + nw, tiles - 1));
     const uint64_t mw = tt >= 0 ? mword >> (16 * (tt & 3) + 4 * qd) : ~0ull;
     float p[4], mx = -INFINITY;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const bool ok = row0 + 4 * qd + r <= last && ((mw >> r) & 1ull);
-      p[r] = ok ? s0[r] + s1[r] : -INFINITY;
+      p[r] = ok ? score[r] : -INFINITY;
       mx = fmaxf(mx, p[r]);
     }
     mx = fmaxf(mx, shfl_xor_f(mx, 16));
     mx = fmaxf(mx, shfl_xor_f(mx, 32));
-    const float m_new = fmaxf(m_run, mx), base = m_new == -INFINITY ? 0.f : m_new;
-    const float alpha = exp2f(m_run - base);
-    m_run = m_new;
+    // The reference exponent is an integer, so that the factors between
+    // tiles and between waves are powers of two and round nothing.
+    const float m_new = fmaxf(m_run, ceilf(mx)), base = m_new == -INFINITY ? 0.f : m_new;
+    if (__any(m_new > m_run)) {
+      const float alpha = exp2f(m_run - base);
+      l_run *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < KS; ++dt) o[dt] *= alpha;
+      m_run = m_new;
+    }
 #pragma unroll
     for (int r = 0; r < 4; ++r) p[r] = exp2f(p[r] - base);
-    l_run = l_run * alpha + ((p[0] + p[1]) + (p[2] + p[3]));
-#pragma unroll
-    for (int dt = 0; dt < KS; ++dt) o[dt] *= alpha;
+    l_run += (p[0] + p[1]) + (p[2] + p[3]);
     // A row of V that is not finite counts only for the query rows that see
     // it: a tree tile that holds one is added key by key instead.
     bool odd = false;
@@ -986,10 +1003,13 @@ __global__ __launch_bounds__(64 * 1024 / D) void tree_attn_f32_kernel(const floa
         }
     } else {
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
+      for (int dt = 0; dt < KS; ++dt) {  // two chains of eight keys
+        f32x4 pv[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-        for (int dt = 0; dt < KS; ++dt)
-          o[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[r][dt >> 2][dt & 3], p[r], o[dt], 0, 0, 0);
+        for (int r = 0; r < 4; ++r)
+          pv[r & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[r][dt >> 2][dt & 3], p[r], pv[r & 1], 0, 0, 0);
+        o[dt] += pv[0] + pv[1];
+      }
     }
   }
   l_run += shfl_xor_f(l_run, 16);
