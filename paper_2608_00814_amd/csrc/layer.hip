@@ -63,10 +63,12 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ 
   const int n = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const float* row = h + (size_t)n * H;
   f32x4 v[kNormVec];
+  u32x2 wv[kNormVec];
   float ss = 0.f;
 #pragma unroll
   for (int i = 0; i < kNormVec; ++i) {
     const int c = 4 * (threadIdx.x + 256 * i);
+    wv[i] = c < H ? *reinterpret_cast<const u32x2*>(w + c) : u32x2{0u, 0u};
     v[i] = c < H ? *reinterpret_cast<const f32x4*>(row + c) : f32x4{0.f, 0.f, 0.f, 0.f};
   }
 #pragma unroll
@@ -82,10 +84,11 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ 
   for (int i = 0; i < kNormVec; ++i) {
     const int c = 4 * (threadIdx.x + 256 * i);
     if (c < H) {
-      const u32x2 wv = *reinterpret_cast<const u32x2*>(w + c);
       u32x2 o;
-      o[0] = pack_bf16x2(v[i][0] * r * __uint_as_float(wv[0] << 16), v[i][1] * r * __uint_as_float(wv[0] & 0xFFFF0000u));
-      o[1] = pack_bf16x2(v[i][2] * r * __uint_as_float(wv[1] << 16), v[i][3] * r * __uint_as_float(wv[1] & 0xFFFF0000u));
+      o[0] = pack_bf16x2(v[i][0] * r * __uint_as_float(wv[i][0] << 16),
+                         v[i][1] * r * __uint_as_float(wv[i][0] & 0xFFFF0000u));
+      o[1] = pack_bf16x2(v[i][2] * r * __uint_as_float(wv[i][1] << 16),
+                         v[i][3] * r * __uint_as_float(wv[i][1] & 0xFFFF0000u));
       *reinterpret_cast<u32x2*>(out + (size_t)n * H + c) = o;
     }
   }
@@ -115,29 +118,33 @@ __global__ __launch_bounds__(1024) void qk_norm_rope_kernel(const uint16_t* __re
   if (hh >= nh) return;
   const uint16_t* src = qkv + (size_t)n * nh * D;
   const long long row = (long long)P + n;  // node n's cache row
-  const bool act = lane < HALF;
-  float cs = 1.f, sn = 0.f;
-  if (act) rope_sincos(P + depth[n], fr.f[lane], sn, cs);
-  {
-    const uint16_t* hr = src + (size_t)hh * D;
-    if (hh >= Hq + Hkv) {
-      const int g = hh - Hq - Hkv;
-      uint16_t* dst = v_cache + ((size_t)g * cap + row) * D;
-      if (act) {
-        dst[lane] = hr[lane];
-        dst[lane + HALF] = hr[lane + HALF];
-      }
-      return;
-    }
-    const bool is_q = hh < Hq;
-    float a = act ? bf16_bits_to_f32(hr[lane]) : 0.f;
-    float b = act ? bf16_bits_to_f32(hr[lane + HALF]) : 0.f;
-    norm_rotate(a, b, act, is_q ? q_norm : k_norm, eps, D, lane, cs, sn);
-    uint16_t* dst = is_q ? q_out + ((size_t)n * Hq + hh) * D : k_cache + ((size_t)(hh - Hq) * cap + row) * D;
+  const bool act = lane < HALF, is_q = hh < Hq;
+  const uint16_t* hr = src + (size_t)hh * D;
+  if (hh >= Hq + Hkv) {
+    const int g = hh - Hq - Hkv;
+    uint16_t* dst = v_cache + ((size_t)g * cap + row) * D;
     if (act) {
-      dst[lane] = f32_to_bf16_bits(a);
-      dst[lane + HALF] = f32_to_bf16_bits(b);
+      dst[lane] = hr[lane];
+      dst[lane + HALF] = hr[lane + HALF];
     }
+    return;
+  }
+  const uint16_t* nw = is_q ? q_norm : k_norm;
+  float a = 0.f, b = 0.f, wa = 1.f, wb = 1.f, cs = 1.f, sn = 0.f;
+  if (act) {
+    a = bf16_bits_to_f32(hr[lane]);
+    b = bf16_bits_to_f32(hr[lane + HALF]);
+    if (nw) {
+      wa = bf16_bits_to_f32(nw[lane]);
+      wb = bf16_bits_to_f32(nw[lane + HALF]);
+    }
+    rope_sincos(P + depth[n], fr.f[lane], sn, cs);
+  }
+  norm_rotate(a, b, nw != nullptr, wa, wb, eps, D, cs, sn);
+  uint16_t* dst = is_q ? q_out + ((size_t)n * Hq + hh) * D : k_cache + ((size_t)(hh - Hq) * cap + row) * D;
+  if (act) {
+    dst[lane] = f32_to_bf16_bits(a);
+    dst[lane + HALF] = f32_to_bf16_bits(b);
   }
 }
 

@@ -284,28 +284,30 @@ __global__ __launch_bounds__(256) void lmhead_f32_kernel(const float* __restrict
   if (wave < NB && qd == 0 && n < N) partial[(size_t)blockIdx.x * N + n] = best;
 }
 
-// One block per node: best of the per-block winners.
+// One block per node: best of the per-block winners, by shuffles in a wave and
+// one barrier (a tree through LDS takes eight).
 __global__ __launch_bounds__(256) void lmhead_finalize_kernel(const Cand* __restrict__ partial, int blocks, int N,
                                                               int32_t* __restrict__ ids, float* __restrict__ maxv) {
-  __shared__ Cand red[256];
+  __shared__ Cand red[4];
   const int n = blockIdx.x;
   Cand b{-INFINITY, 0x7FFFFFFF};
   for (int i = threadIdx.x; i < blocks; i += 256) {
     const Cand o = partial[(size_t)i * N + n];
     if (better(o.v, o.i, b.v, b.i)) b = o;
   }
-  red[threadIdx.x] = b;
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if (threadIdx.x < off) {
-      const Cand o = red[threadIdx.x + off];
-      if (better(o.v, o.i, red[threadIdx.x].v, red[threadIdx.x].i)) red[threadIdx.x] = o;
-    }
-    __syncthreads();
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    const Cand o{shfl_xor_f(b.v, off), shfl_xor_i(b.i, off)};
+    if (better(o.v, o.i, b.v, b.i)) b = o;
   }
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = b;
+  __syncthreads();
   if (threadIdx.x == 0) {
-    ids[n] = red[0].i;
-    maxv[n] = red[0].v;
+#pragma unroll
+    for (int w = 1; w < 4; ++w)
+      if (better(red[w].v, red[w].i, b.v, b.i)) b = red[w];
+    ids[n] = b.i;
+    maxv[n] = b.v;
   }
 }
 

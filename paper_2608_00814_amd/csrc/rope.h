@@ -34,20 +34,18 @@ __device__ __forceinline__ void rope_sincos(int pos, double f, float& sn, float&
   sincosf((float)red, &sn, &cs);
 }
 
-// Lanes j < D/2 (act) hold the rotate-half pair (a, b) = (x[j], x[j + D/2])
-// of one head; every lane of the wave calls this (the norm's sum of squares
-// is a wave reduction).  Optional RMSNorm with weight nw (null: none), then
-// the rotation by the angle whose sine and cosine are sn, cs.
-__device__ __forceinline__ void norm_rotate(float& a, float& b, bool act, const uint16_t* nw, float eps, int D,
-                                            int lane, float cs, float sn) {
-  if (nw) {
+// Lanes j < D/2 hold the rotate-half pair (a, b) = (x[j], x[j + D/2]) of one
+// head, the others zeros; every lane of the wave calls this (the norm's sum
+// of squares is a wave reduction).  Optional RMSNorm with the pair's weights
+// wa, wb, then the rotation by the angle whose sine and cosine are sn, cs.
+__device__ __forceinline__ void norm_rotate(float& a, float& b, bool norm, float wa, float wb, float eps, int D,
+                                            float cs, float sn) {
+  if (norm) {
     float ss = __builtin_fmaf(a, a, b * b);
     for (int off = 32; off > 0; off >>= 1) ss += shfl_xor_f(ss, off);
     const float r = 1.f / sqrtf(ss / (float)D + eps);
-    if (act) {
-      a = a * r * bf16_bits_to_f32(nw[lane]);
-      b = b * r * bf16_bits_to_f32(nw[lane + D / 2]);
-    }
+    a = a * r * wa;
+    b = b * r * wb;
   }
   const float ra = a * cs - b * sn, rb = b * cs + a * sn;
   a = ra;
