@@ -65,6 +65,7 @@ struct AttnArgs {
   int splits, row_blocks, Mpad, tiles_prefix, tiles_total;
   int tps;           // key tiles per split (split s takes tiles [s tps, (s + 1) tps))
   uint32_t g_inv;    // ceil(2^32 / G) (0 for G = 1): row / G is one multiplication
+  int rows_first;    // order of the work items (see the launch)
   const int* P_dev;  // null, or the prefix length in device memory (P bounds it)
 };
 
@@ -196,11 +197,12 @@ __global__ __launch_bounds__(64 * RG * (SPLIT ? 2 : 1)) void tree_attn_bf16_kern
   uint8_t* const vst[R::NS] = {v0, v1, v2, v3};
 
   const int total = a.Hkv * a.row_blocks * a.splits;
-  int w = xcd_order(blockIdx.x, total);
-  const int s = w % a.splits;
-  w /= a.splits;
-  const int rb = w % a.row_blocks;
-  const int g = w / a.row_blocks;
+  const int w = xcd_order(blockIdx.x, total);
+  // items in order (head, row block, split), or (head, split, row block)
+  const int inner = a.rows_first ? a.row_blocks : a.splits, outer = a.rows_first ? a.splits : a.row_blocks;
+  const int x = w % inner, y = w / inner % outer;
+  const int s = a.rows_first ? y : x, rb = a.rows_first ? x : y;
+  const int g = w / inner / outer;
   // The prefix length is the launch value or, for replays of one captured
   // step at a growing prefix, the value in device memory (clamped to the
   // launch value, which the plan and the validation used).
@@ -217,7 +219,10 @@ __global__ __launch_bounds__(64 * RG * (SPLIT ? 2 : 1)) void tree_attn_bf16_kern
   const int t_begin = s * tps;
   const int t_end = min(t_begin + tps, tiles_total);
   const int ntiles = t_end - t_begin;
-  const bool early = ntiles > 1 && tps <= kEarlyTiles;  // key-split kernel: tile 1 requested together with tile 0
+  // Key-split kernel over a short run of tiles (by the plan, which is known
+  // before the prefix length): K of tile 0 is requested ahead of the queries
+  // and tile 1 together with tile 0.
+  const bool short_run = a.tps <= kEarlyTiles, early = ntiles > 1 && short_run;
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint32_t wave_u = __builtin_amdgcn_readfirstlane(wave);
@@ -322,9 +327,7 @@ __global__ __launch_bounds__(64 * RG * (SPLIT ? 2 : 1)) void tree_attn_bf16_kern
     // ring stage 3 (rows 0..63 in k3, 64..127 in v3): tile 3 is not
     // requested before every wave has read its fragments.  Mask words go
     // to mwords as [row][W] (dword DMA, 64 dwords per instruction).
-    // K of the first tile is requested before them (their addresses take a
-    // while to form) and its V after them.
-    issue_kv(t_begin, std::integral_constant<int, 0>{}, true, false);
+    if (short_run) issue_kv(t_begin, std::integral_constant<int, 0>{}, true, false);
     const auto row_src = [&](int r) OOO_INLINE {
       const int rq = min(rb * BM + r, a.M - 1);
       return row_node(rq, a.G, a.g_inv);
@@ -353,7 +356,7 @@ __global__ __launch_bounds__(64 * RG * (SPLIT ? 2 : 1)) void tree_attn_bf16_kern
   // node and a 4k prefix (3 tiles a split), 14.4 -> 14.2 at 64 nodes (6),
   // but 43.7 -> 44.3 at 256 nodes and 16k (33 tiles).
   if constexpr (SPLIT) {
-    issue_kv(t_begin, std::integral_constant<int, 0>{}, false, true);
+    issue_kv(t_begin, std::integral_constant<int, 0>{}, !short_run, true);
     if (early) issue(t_begin + 1, std::integral_constant<int, 1>{});
   } else {
     issue(t_begin, std::integral_constant<int, 0>{});
@@ -806,7 +809,7 @@ __global__ __launch_bounds__(64 * RG * (SPLIT ? 2 : 1)) void tree_attn_bf16_kern
 // 9.96 against one 9.74 us.
 constexpr int kCombineWaves = 1;
 
-template <int D, int SMAX>
+template <int D, int SMAX, int CH>
 __global__ __launch_bounds__(64 * kCombineWaves) void tree_attn_combine_kernel(AttnArgs a) {
   constexpr int NP = D / 16;  // group pairs per lane
   const int lane = threadIdx.x & 63;
@@ -825,30 +828,39 @@ __global__ __launch_bounds__(64 * kCombineWaves) void tree_attn_combine_kernel(A
   const size_t split_ml = (size_t)a.Hkv * a.Mpad;         // rows between consecutive splits
   const u32x4* po = reinterpret_cast<const u32x4*>(a.part_o) + (((size_t)g * nblk + blk) * NP + k) * 64 + lane;
   const f32x2_t* pml = reinterpret_cast<const f32x2_t*>(a.part_ml) + (size_t)g * a.Mpad + r;
-  f32x2_t ml[SMAX];
-  u32x4 o[SMAX];
-#pragma unroll
-  for (int s = 0; s < SMAX; ++s) {  // splits past the count re-read the last one (weight zero below)
-    const int sc = min(s, a.splits - 1);
-    ml[s] = pml[sc * split_ml];
-    o[s] = po[sc * split_o];
-  }
-  float m = -INFINITY;
-#pragma unroll
-  for (int s = 0; s < SMAX; ++s) m = s < a.splits ? __builtin_fmaxf(m, ml[s][0]) : m;
-  const float base = m == -INFINITY ? 0.f : m;
-  float den = 0.f;
+  float m = -INFINITY, den = 0.f;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int s = 0; s < SMAX; ++s) {
-    const float wgt = s < a.splits ? __builtin_amdgcn_exp2f(ml[s][0] - base) : 0.f;
-    den += wgt;
-    const float wv2 = __builtin_amdgcn_ldexpf(wgt, (int)ml[s][1]);
+  for (int ch = 0; ch < CH; ++ch) {
+    f32x2_t ml[SMAX];
+    u32x4 o[SMAX];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const f32x2_t h = unpack_f16x2(o[s][e]);
-      acc[2 * e] += wv2 * h[0];
-      acc[2 * e + 1] += wv2 * h[1];
+    for (int s = 0; s < SMAX; ++s) {  // splits past the count re-read the last one (weight zero below)
+      const int sc = min(ch * SMAX + s, a.splits - 1);
+      ml[s] = pml[sc * split_ml];
+      o[s] = po[sc * split_o];
+    }
+    const float m_old = m;
+#pragma unroll
+    for (int s = 0; s < SMAX; ++s) m = ch * SMAX + s < a.splits ? __builtin_fmaxf(m, ml[s][0]) : m;
+    const float base = m == -INFINITY ? 0.f : m;
+    if (ch > 0) {
+      const float alpha = __builtin_amdgcn_exp2f(m_old - base);
+      den *= alpha;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[e] *= alpha;
+    }
+#pragma unroll
+    for (int s = 0; s < SMAX; ++s) {
+      const float wgt = ch * SMAX + s < a.splits ? __builtin_amdgcn_exp2f(ml[s][0] - base) : 0.f;
+      den += wgt;
+      const float wv2 = __builtin_amdgcn_ldexpf(wgt, (int)ml[s][1]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const f32x2_t h = unpack_f16x2(o[s][e]);
+        acc[2 * e] += wv2 * h[0];
+        acc[2 * e + 1] += wv2 * h[1];
+      }
     }
   }
   const float inv = 1.f / den;
@@ -1036,10 +1048,10 @@ __global__ __launch_bounds__(64 * 1024 / D) void tree_attn_f32_kernel(const floa
 
 // The combine kernel loads exactly the splits there are (up to 16; more in
 // groups of 4): each padding slot is one more load per lane, and the merge
-// is bound by its loads.
-template <int D, int S>
+// is bound by its loads.  More than 32 splits are merged in two batches.
+template <int D, int S, int CH = 1>
 void launch_combine_n(dim3 grid, hipStream_t st, const AttnArgs& a) {
-  tree_attn_combine_kernel<D, S><<<grid, 64 * kCombineWaves, 0, st>>>(a);
+  tree_attn_combine_kernel<D, S, CH><<<grid, 64 * kCombineWaves, 0, st>>>(a);
 }
 template <int D>
 void launch_combine(int splits, dim3 grid, hipStream_t st, const AttnArgs& a) {
@@ -1063,7 +1075,9 @@ void launch_combine(int splits, dim3 grid, hipStream_t st, const AttnArgs& a) {
       if (splits <= 20) return launch_combine_n<D, 20>(grid, st, a);
       if (splits <= 24) return launch_combine_n<D, 24>(grid, st, a);
       if (splits <= 28) return launch_combine_n<D, 28>(grid, st, a);
-      return launch_combine_n<D, 32>(grid, st, a);
+      if (splits <= 32) return launch_combine_n<D, 32>(grid, st, a);
+      if (splits <= 48) return launch_combine_n<D, 24, 2>(grid, st, a);
+      return launch_combine_n<D, 32, 2>(grid, st, a);
   }
 }
 
@@ -1088,22 +1102,26 @@ Plan make_plan(int N, int Hq, int Hkv, int D, int P, ooo_dtype dt, int force_spl
   // tiles of the busiest split against the merge of the partials: a tile
   // costs about 1 us, a split 0.1 us (0.15 us where the blocks themselves are
   // cheap: 64 rows of 64) and the merge, a second launch, 0.5 us more than the
-  // work it takes off the blocks, 1 us for few rows (units of 0.05 us; fitted to graphs of calls over 196 shapes: 1 to 256
-  // nodes, prefixes 40 to 16384, 1 to 8 KV heads, head_dim 64 and 128, and
-  // every split count).  The earlier 1.3 us per tile and 0.25 to 0.5 us per
+  // work it takes off the blocks, 1 us for few rows, 2 us more where more than
+  // 32 splits take a second batch of loads (units of 0.05 us; fitted to graphs
+  // of calls over 196 shapes: 1 to 256 nodes, prefixes 40 to 16384, 1 to 8 KV
+  // heads, head_dim 64 and 128, and every split count).  The earlier 1.3 us per tile and 0.25 to 0.5 us per
   // split chose too few splits where the blocks do not fill the chip: 100
   // nodes x 8 heads of 64 at prefix 1024 took 9.6 us with 6 splits and
   // 7.9 us with 18.
+  // Up to 64 splits: one node x 4 heads on one KV head at prefix 40000 took
+  // 29.3 us with 32 (20 tiles each) and takes 23.0 with 63; at 16384 (9 tiles)
+  // more than 32 lose as often as they gain.
   const int base = Hkv * p.row_blocks;
   const int max_splits = device_cus() / base > 1 ? device_cus() / base : 1;
   const int split_cost = D == 64 && p.waves == 2 ? 3 : 2, merge_cost = M <= 32 ? 20 : 10;
   int splits = 1, best = INT32_MAX;
-  for (int sc = 1; sc <= max_splits && sc <= p.tiles_total; ++sc) {
-    const int cost = 20 * ((p.tiles_total + sc - 1) / sc) + split_cost * sc + (sc > 1 ? merge_cost : 0);
+  for (int sc = 1; sc <= max_splits && sc <= p.tiles_total && sc <= 64; ++sc) {
+    const int cost = 20 * ((p.tiles_total + sc - 1) / sc) + split_cost * sc + (sc > 1 ? merge_cost : 0) +
+                     (sc > 32 ? 40 : 0);
     if (cost < best) best = cost, splits = sc;
   }
-  if (force_splits > 0) splits = force_splits;
-  if (splits > 32) splits = 32;
+  if (force_splits > 0) splits = force_splits < 32 ? force_splits : 32;
   if (splits > p.tiles_total) splits = p.tiles_total;
   if (splits < 1) splits = 1;
   // fixed-size runs of tiles; the last run may be shorter
@@ -1201,6 +1219,14 @@ extern "C" int ooo_tree_attn_ex(const void* q, const void* k_cache, const void* 
     a.tiles_prefix = p.tiles_prefix;
     a.tiles_total = p.tiles_total;
     a.tps = p.tps;
+    // With fewer KV heads than XCDs a head's work spreads over several.  Over
+    // long runs of tiles an XCD then takes all row blocks of some splits, so
+    // that K and V come into one L2 instead of each; over short ones all
+    // splits of some row blocks, whose partials its combine blocks re-read.
+    // 256 nodes x 4 heads on one KV head at prefix 40000 39.6 -> 32.7 us per
+    // call, 100 x 14 on 2 at 16384 (13 tiles a split) 25.4 -> 24.2, but at
+    // 1024 (2 tiles) 11.4 -> 12.6.
+    a.rows_first = n_kv_heads < 8 && p.tps >= 8;
     a.g_inv = G > 1 ? (uint32_t)(((1ull << 32) + G - 1) / G) : 0u;
     if (p.splits > 1) {
       a.part_o = (uint32_t*)workspace;

@@ -238,6 +238,10 @@ PLAN_EDGES = [
     (1984, 40, 7, 3, 128, 5),  # 3 row blocks x 3 heads x 5 splits: a grid that is no multiple of 8; rows / 7
     (500, 33, 13, 1, 64, 3),   # 4 row blocks x 3 splits; rows / 13
     (300, 3, 1000, 1, 128, 2),  # more query heads a KV head than rows in a block
+    (1500, 60, 5, 3, 128, 3),  # runs of 9 tiles on 3 KV heads: row blocks ordered inside splits (3 x 3 x 3 blocks)
+    (900, 60, 3, 2, 64, 2),
+    (30000, 3, 1, 1, 64, 0),  # more than 32 splits: merged in two batches of loads
+    (40000, 2, 4, 1, 128, 0),
 ]
 
 
