@@ -1127,8 +1127,15 @@ Plan make_plan(int N, int Hq, int Hkv, int D, int P, ooo_dtype dt, int force_spl
   // fixed-size runs of tiles; the last run may be shorter
   p.tps = (p.tiles_total + splits - 1) / splits;
   p.splits = (p.tiles_total + p.tps - 1) / p.tps;
-  if (p.splits > 1)
-    p.ws_bytes = (size_t)p.splits * Hkv * p.Mpad * (size_t)D * 2 + (size_t)p.splits * Hkv * p.Mpad * 8 + 256;
+  // Scratch for the most splits that any prefix up to this one may get (at
+  // most as many blocks as CUs), so that a workspace sized for a prefix
+  // serves every shorter one.
+  int most = p.splits;
+  if (force_splits <= 0) {
+    most = max_splits < 64 ? max_splits : 64;
+    if (most > p.tiles_total) most = p.tiles_total;
+  }
+  if (most > 1) p.ws_bytes = (size_t)most * Hkv * p.Mpad * (size_t)D * 2 + (size_t)most * Hkv * p.Mpad * 8 + 256;
   return p;
 }
 

@@ -272,3 +272,12 @@ def test_device_entry_points_validate_on_host():
     assert L.ooo_tree_attn(fake, fake, fake, 4160, 4096, None, 64, fake, 1, 32, 8, 128, 0.1, ooo.BF16, fake, fake,
                            need - 1, None) == ooo.ERR_CAPACITY
     assert ooo.last_error() != ""
+
+
+@pytest.mark.parametrize("Hq,Hkv,D", [(32, 8, 128), (14, 2, 128), (4, 1, 64), (40, 8, 128)])
+def test_attention_workspace_of_a_prefix_serves_shorter_ones(Hq, Hkv, D):
+    size = lambda n, P: ooo.tree_attn_workspace(n, Hq, Hkv, D, P, ooo.BF16)
+    for n in (1, 7, 16, 33, 64, 100, 129, 256):
+        sizes = [size(n, P) for P in (1, 63, 65, 200, 1000, 1024, 4096, 9000, 16384, 30000, 40000)]
+        assert sizes == sorted(sizes)
+        assert sizes[-1] <= ooo.lib().ooo_tree_attn_noalloc_scratch_bytes()
