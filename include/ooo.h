@@ -177,11 +177,16 @@ int ooo_hint_merge(const int32_t* bank, int64_t bank_len, int32_t eos_token, con
  * workspace, ws_bytes  device scratch of ooo_tree_attn_workspace() bytes (0
  *            when the plan needs none; then workspace may be NULL): the bf16
  *            path splits the keys over workgroups, and a second kernel on the
- *            same stream merges the splits' partial results from it.
+ *            same stream merges the splits' partial results from it.  The
+ *            query does not decrease with n_nodes or prefix_len: a workspace
+ *            for a trie size and prefix serves every smaller trie and shorter
+ *            prefix of the same head counts and head_dim.  (A trie too wide to
+ *            split, n_kv_heads times its row blocks above half the compute
+ *            units, needs none itself.)
  * Errors: OOO_ERR_INVALID (null pointers, n_nodes < 1, prefix_len < 0,
  * P + n_nodes > cap, n_q_heads % n_kv_heads != 0, 64 * mask_words < n_nodes),
- * OOO_ERR_UNSUPPORTED, OOO_ERR_CAPACITY (ws_bytes below the query),
- * OOO_ERR_HIP.
+ * OOO_ERR_UNSUPPORTED, OOO_ERR_CAPACITY (ws_bytes below the query, but for
+ * tries too wide to split), OOO_ERR_HIP.
  *
  * Relative to the plain signature of this step (Q, the layer's K/V cache, P,
  * N, the ancestor masks, head counts, scale, dtype, out, workspace, stream),

@@ -1083,7 +1083,8 @@ void launch_combine(int splits, dim3 grid, hipStream_t st, const AttnArgs& a) {
 
 struct Plan {
   int waves, row_blocks, Mpad, tiles_prefix, tiles_total, splits, tps;
-  size_t ws_bytes;
+  size_t ws_bytes;    // the query's answer
+  size_t call_bytes;  // what a call checks for: 0 where this trie is too wide to split
 };
 
 // force_splits > 0 replaces the planner's split count (tests and tuning).
@@ -1127,15 +1128,20 @@ Plan make_plan(int N, int Hq, int Hkv, int D, int P, ooo_dtype dt, int force_spl
   // fixed-size runs of tiles; the last run may be shorter
   p.tps = (p.tiles_total + splits - 1) / splits;
   p.splits = (p.tiles_total + p.tps - 1) / p.tps;
-  // Scratch for the most splits that any prefix up to this one may get (at
-  // most as many blocks as CUs), so that a workspace sized for a prefix
-  // serves every shorter one.
-  int most = p.splits;
+  // Scratch.  A plan that splits never has more blocks than CUs, nor more
+  // splits than 64 or than there are tiles; the query counts the blocks of a
+  // KV head that these bounds allow, which no smaller trie and no shorter
+  // prefix exceeds, so one workspace serves them all.  A forced split count
+  // asks for exactly its own partials.
+  long long blocks = (long long)p.splits * p.row_blocks;
+  bool wanted = p.splits > 1;
   if (force_splits <= 0) {
-    most = max_splits < 64 ? max_splits : 64;
-    if (most > p.tiles_total) most = p.tiles_total;
+    blocks = (long long)(p.tiles_total < 64 ? p.tiles_total : 64) * p.row_blocks;
+    if (blocks > device_cus() / Hkv) blocks = device_cus() / Hkv;
+    wanted = p.tiles_total > 1 && blocks > 1;
   }
-  if (most > 1) p.ws_bytes = (size_t)most * Hkv * p.Mpad * (size_t)D * 2 + (size_t)most * Hkv * p.Mpad * 8 + 256;
+  if (wanted) p.ws_bytes = (size_t)(blocks * Hkv * BM) * (size_t)(2 * D + 8) + 256;
+  p.call_bytes = force_splits > 0 || max_splits > 1 ? p.ws_bytes : 0;
   return p;
 }
 
@@ -1202,8 +1208,8 @@ extern "C" int ooo_tree_attn_ex(const void* q, const void* k_cache, const void* 
                                                           (float*)out);
   } else {
     const Plan p = make_plan(n_nodes, n_q_heads, n_kv_heads, head_dim, prefix_len, dt, force_splits);
-    OOO_REQUIRE(ws_bytes >= p.ws_bytes && (p.ws_bytes == 0 || workspace), OOO_ERR_CAPACITY,
-                "ooo_tree_attn: workspace of %zu bytes needed (got %zu)", p.ws_bytes, ws_bytes);
+    OOO_REQUIRE(ws_bytes >= p.call_bytes && (p.call_bytes == 0 || workspace), OOO_ERR_CAPACITY,
+                "ooo_tree_attn: workspace of %zu bytes needed (got %zu)", p.call_bytes, ws_bytes);
     AttnArgs a{};
     a.q = (const uint16_t*)q;
     a.k = (const uint16_t*)k_cache;

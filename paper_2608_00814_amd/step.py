@@ -76,10 +76,7 @@ class VerifyRunner:
         self.path = self.res[2:]
         self.h_res = torch.zeros_like(self.res, device="cpu").pin_memory()
         self.attn_ws = torch.zeros(64, dtype=torch.float32, device=dev)
-        # the scratch of any trie size at any prefix up to max_prefix
-        self.ensure_workspace(max(max_prefix, 1), max(
-            range(1, max_nodes + 1),
-            key=lambda nn: ooo.tree_attn_workspace(nn, n_q_heads, n_kv_heads, head_dim, max(max_prefix, 1), self.code)))
+        self.ensure_workspace(max(max_prefix, 1), max_nodes)  # serves smaller tries and shorter prefixes too
         lws = ooo.lmhead_workspace(max_nodes, hidden, vocab, self.code)
         self.lm_ws = torch.empty(max(lws, 256) // 4 + 1, dtype=torch.float32, device=dev)
         self.scale = 1.0 / math.sqrt(head_dim)

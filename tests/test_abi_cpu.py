@@ -281,3 +281,17 @@ def test_attention_workspace_of_a_prefix_serves_shorter_ones(Hq, Hkv, D):
         sizes = [size(n, P) for P in (1, 63, 65, 200, 1000, 1024, 4096, 9000, 16384, 30000, 40000)]
         assert sizes == sorted(sizes)
         assert sizes[-1] <= ooo.lib().ooo_tree_attn_noalloc_scratch_bytes()
+
+
+@pytest.mark.parametrize("Hq,Hkv,D", [(32, 8, 128), (14, 2, 128), (4, 1, 64), (40, 8, 128), (16, 8, 128), (64, 64, 64)])
+def test_attention_workspace_serves_every_smaller_trie(Hq, Hkv, D):
+    """What the query returns for a trie size and prefix covers every smaller
+    trie at every shorter prefix; a call asks for what the query returns."""
+    prefixes = (0, 1, 40, 64, 200, 900, 960, 1024, 4032, 4096, 9000, 40000)
+    last = None
+    for N in list(range(1, 257)) + [300, 512, 600, 1024]:
+        sizes = [ooo.tree_attn_workspace(N, Hq, Hkv, D, P, ooo.BF16) for P in prefixes]
+        assert sizes == sorted(sizes)
+        assert last is None or all(a <= b for a, b in zip(last, sizes)), N
+        last = sizes
+    assert last[-1] <= ooo.lib().ooo_tree_attn_noalloc_scratch_bytes()

@@ -322,6 +322,26 @@ def test_attention_workspace_reuse_across_shapes():
         assert gh.row_rel_err(got, ref) <= gh.ATTN_TOL
 
 
+def test_attention_workspace_of_a_trie_serves_smaller_ones():
+    """A workspace sized for 96 nodes at prefix 4096 serves smaller tries and
+    shorter prefixes, with the results their own workspaces give."""
+    print("case attention workspace of a larger trie", flush=True)
+    Hq, Hkv, D = 32, 8, 128
+    rs, q, k, v, cap = _attn_inputs(4096, 96, Hq // Hkv, Hkv, D, "bf16", seed=96)
+    kd, vd = gh.to_dev(k, "bf16", DEV), gh.to_dev(v, "bf16", DEV)
+    ws = torch.full((ooo.tree_attn_workspace(96, Hq, Hkv, D, 4096, ooo.BF16) // 4,), float("nan"), device=DEV)
+    for n, P in [(96, 4096), (64, 4096), (64, 960), (33, 4032), (16, 960), (1, 4096)]:
+        mask = torch.from_numpy(ov.ancestor_masks(_trie("random", n, rs)["parent"], (n + 63) // 64).view(np.int64)).to(DEV)
+        own = torch.full((ooo.tree_attn_workspace(n, Hq, Hkv, D, P, ooo.BF16) // 4,), float("nan"), device=DEV)
+        outs = []
+        for w in (ws, own):
+            out = torch.full((n, Hq, D), float("nan"), dtype=torch.bfloat16, device=DEV)
+            ooo.tree_attn(gh.to_dev(q[:n], "bf16", DEV), kd, vd, P, n, mask, Hq, Hkv, 1.0 / math.sqrt(D), out, w)
+            torch.cuda.synchronize()
+            outs.append(out)
+        assert torch.isfinite(outs[0]).all() and torch.equal(*outs), (n, P)
+
+
 @pytest.mark.parametrize("dt", ["bf16", "f32"])
 def test_attention_ignores_rows_outside_prefix_and_tree(dt):
     """Cache rows at and beyond P + N hold NaN; the output must not see
