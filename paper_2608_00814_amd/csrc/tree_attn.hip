@@ -903,6 +903,7 @@ __global__ __launch_bounds__(64 * 1024 / D) void tree_attn_f32_kernel(const floa
   constexpr int KS = D / 16;    // 16-column steps of a row
   __shared__ f32x4 o_s[NW][KS][64];
   __shared__ f32x2_t ml_s[NW][16];
+  __shared__ int odd_s[NW];
   if (P_dev) P = min(max(*P_dev, 0), P);
   const int G = Hq / Hkv, M = N * G, row_blocks = (M + 15) / 16;
   const int g = blockIdx.x / row_blocks, rb = blockIdx.x - g * row_blocks;
@@ -990,38 +991,13 @@ __global__ __launch_bounds__(64 * 1024 / D) void tree_attn_f32_kernel(const floa
 #pragma unroll
     for (int r = 0; r < 4; ++r) p[r] = exp2f(p[r] - base);
     l_run += (p[0] + p[1]) + (p[2] + p[3]);
-    // A row of V that is not finite counts only for the query rows that see
-    // it: a tree tile that holds one is added key by key instead.
-    bool odd = false;
-    if (tt >= 0) {
+#pragma unroll
+    for (int dt = 0; dt < KS; ++dt) {  // two chains of eight keys
+      f32x4 pv[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
       for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int h = 0; h < D / 64; ++h)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) odd |= !(__builtin_fabsf(vv[r][h][e]) < INFINITY);
-    }
-    if (__any(odd)) {
-      for (int q4 = 0; q4 < 4; ++q4)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const float pk = __shfl(p[r], 16 * q4 + c, kWave);
-          if (pk == 0.f) continue;
-          const float* vr = vb + (size_t)min(row0 + 4 * q4 + r, last) * D + 16 * qd;
-#pragma unroll
-          for (int dt = 0; dt < KS; ++dt)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[dt][e] += pk * vr[64 * (dt >> 2) + 4 * e + (dt & 3)];
-        }
-    } else {
-#pragma unroll
-      for (int dt = 0; dt < KS; ++dt) {  // two chains of eight keys
-        f32x4 pv[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          pv[r & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[r][dt >> 2][dt & 3], p[r], pv[r & 1], 0, 0, 0);
-        o[dt] += pv[0] + pv[1];
-      }
+        pv[r & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[r][dt >> 2][dt & 3], p[r], pv[r & 1], 0, 0, 0);
+      o[dt] += pv[0] + pv[1];
     }
   }
   l_run += shfl_xor_f(l_run, 16);
@@ -1029,10 +1005,60 @@ __global__ __launch_bounds__(64 * 1024 / D) void tree_attn_f32_kernel(const floa
 #pragma unroll
   for (int dt = 0; dt < KS; ++dt) o_s[wave][dt][lane] = o[dt];
   if (qd == 0) ml_s[wave][c] = f32x2_t{m_run, l_run};
+  f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int dt = 0; dt < KS; ++dt) zero += o[dt] * 0.f;
+  const int odd = __any(!((zero[0] + zero[1]) + (zero[2] + zero[3]) == 0.f));
+  if (lane == 0) odd_s[wave] = odd;
   __syncthreads();
-  if (wave >= KS || row >= M) return;  // wave dt adds accumulator dt
   float m = -INFINITY, den = 0.f;
   for (int w = 0; w < nw; ++w) m = fmaxf(m, ml_s[w][c][0]);
+  // A value of V that is not finite counts only for the query rows that give
+  // its key a weight, but the matrix products multiply it by the zeros of the
+  // others too (masked keys, a tail's repeated rows, keys whose probability
+  // vanishes in float), and zero times it is NaN.  So where a wave's sums are
+  // not finite the block adds its keys once more, one by one and relative to
+  // the rows' final exponents, without those of weight zero.  (Looking V over
+  // tile by tile cost 2 to 4 % of every call.)
+  if (__any(lane < nw && odd_s[lane])) {
+    __syncthreads();  // every wave has read ml_s and odd_s
+    // The queries are read again: with qv used here the compiler would wait
+    // for them above, before it requests the first keys (1 us at short prefixes).
+    const float* qr = q + ((size_t)node * Hq + head) * D + 4 * qd;
+    asm("" : "+v"(qr));
+    l_run = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < KS; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = wave; t < tiles; t += nw) {
+      int row0, last;
+      tile_rows(t, row0, last);
+      const int tt = t - tiles_prefix;
+      const uint64_t mword = tt >= 0 ? mask[(size_t)node * W + (tt >> 2)] >> (16 * (tt & 3)) : ~0ull;
+#pragma unroll 1
+      for (int j = 0; j < 16 && row0 + j <= last; ++j) {
+        const float* kr = kb + (size_t)(row0 + j) * D + 4 * qd;
+        f32x4 s4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < KS; ++s) s4 += *reinterpret_cast<const f32x4u*>(kr + 16 * s) * *reinterpret_cast<const f32x4u*>(qr + 16 * s);
+        float sc = ((s4[0] + s4[1]) + (s4[2] + s4[3])) * sl2;
+        sc += shfl_xor_f(sc, 16);
+        sc += shfl_xor_f(sc, 32);
+        const float pk = (mword >> j) & 1ull ? exp2f(sc - m) : 0.f;
+        if (pk == 0.f) continue;
+        l_run += pk;
+        const float* vr = vb + (size_t)(row0 + j) * D + 16 * qd;
+#pragma unroll
+        for (int dt = 0; dt < KS; ++dt)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[dt][e] += pk * vr[64 * (dt >> 2) + 4 * e + (dt & 3)];
+      }
+    }
+#pragma unroll
+    for (int dt = 0; dt < KS; ++dt) o_s[wave][dt][lane] = o[dt];
+    if (qd == 0) ml_s[wave][c] = f32x2_t{m, l_run};
+    __syncthreads();
+  }
+  if (wave >= KS || row >= M) return;  // wave dt adds accumulator dt
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 4
   for (int w = 0; w < nw; ++w) {

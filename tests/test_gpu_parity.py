@@ -296,6 +296,34 @@ def test_attention_f32_rows_not_seen_may_hold_anything(D):
     assert np.isnan(got[7]).any() and np.isnan(got[21, :G, D - 1]).all()
 
 
+@pytest.mark.parametrize("P,D,low", [(50, 64, None), (50, 128, None), (700, 128, None), (50, 64, (0, 16)),
+                                     (700, 128, (0, 16)), (700, 128, (693, 699)), (200, 64, (33, 34))])
+def test_attention_f32_infinite_values_in_the_prefix(P, D, low):
+    """An infinite value of a prefix row reaches the queries that give the row
+    a weight, as an infinity, and no other: not by the rows that pad the last
+    prefix tile (low None: the last row of V holds the infinity), nor by keys
+    whose probability is zero in float32 (low: those rows, whose scores lie
+    350 powers of two below the others', in a tile with others, in a tile of
+    their own, and as the first of a wave's tiles)."""
+    print(f"case attention f32 infinite prefix values P={P} D={D} low={low}", flush=True)
+    N, G, Hkv = 21, 2, 2
+    rs, q, k, v, cap = _attn_inputs(P, N, G, Hkv, D, "f32", seed=P + D)
+    t = _trie("random", N, rs)
+    mask = ov.ancestor_masks(t["parent"], 1)
+    rows = slice(P - 1, P) if low is None else slice(*low)
+    if low is not None:
+        q[..., 0] = 1.0
+        k[:, rows, 0] = -250.0 * math.sqrt(D)
+    v[:, rows, 3] = 0.0
+    ref = ov.tree_attention(wl.to_f64(q, "f32"), wl.to_f64(k, "f32"), wl.to_f64(v, "f32"), P, t["parent"], Hkv)
+    v[:, rows, 3] = np.inf
+    got = _run_attn(q, k, v, P, N, mask, G * Hkv, Hkv, D, "f32")
+    if low is None:
+        assert (got[..., 3] == np.inf).all()
+        got[..., 3] = ref[..., 3]
+    assert gh.row_rel_err(got, ref) <= 1e-5
+
+
 def test_attention_workspace_reuse_across_shapes():
     """One workspace serves calls of different shapes, head sizes and split
     counts in a row: nothing a call reads from it is left over from another
