@@ -1039,8 +1039,10 @@ __global__ __launch_bounds__(64 * 1024 / D) void tree_attn_f32_kernel(const floa
         const float* kr = kb + (size_t)(row0 + j) * D + 4 * qd;
         f32x4 s4 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int s = 0; s < KS; ++s) s4 += *reinterpret_cast<const f32x4u*>(kr + 16 * s) * *reinterpret_cast<const f32x4u*>(qr + 16 * s);
-        float sc = ((s4[0] + s4[1]) + (s4[2] + s4[3])) * sl2;
+        for (int s = 0; s < KS; ++s)
+          s4 += *reinterpret_cast<const f32x4u*>(kr + 16 * s) *
+                (*reinterpret_cast<const f32x4u*>(qr + 16 * s) * sl2);  // scaled as in qv: the same range
+        float sc = (s4[0] + s4[1]) + (s4[2] + s4[3]);
         sc += shfl_xor_f(sc, 16);
         sc += shfl_xor_f(sc, 32);
         const float pk = (mword >> j) & 1ull ? exp2f(sc - m) : 0.f;
