@@ -489,6 +489,7 @@ __global__ __launch_bounds__(1024) void linear_qk_norm_rope_kernel(
 
 struct LinPlan {
   int nb;
+  long long chunks;  // (128-row tile, 64-column chunk) blocks of the weight
   Runs runs;
   size_t val_bytes;  // fp16 partial values (the factors follow)
   size_t ws_bytes;
@@ -502,11 +503,11 @@ LinPlan lin_plan(int N, int K, int O) {
   LinPlan p{};
   p.nb = N <= 32 ? 1 : N <= 64 ? 2 : N <= 128 ? 4 : 8;
   const int KC = K / 64;
-  const int C = (int)((O + (long long)kStreamRows - 1) / kStreamRows) * KC;
-  p.runs.B = C < device_cus() ? C : device_cus();
-  p.runs.q = C / p.runs.B;
-  p.runs.r = C % p.runs.B;
-  p.runs.seg = (p.runs.q + (p.runs.r > 0)) / KC + 2;  // tiles a run can touch
+  p.chunks = (O + (long long)kStreamRows - 1) / kStreamRows * KC;
+  p.runs.B = p.chunks < device_cus() ? (int)p.chunks : device_cus();
+  p.runs.q = (int)(p.chunks / p.runs.B);
+  p.runs.r = (int)(p.chunks % p.runs.B);
+  p.runs.seg = (int)((p.chunks / p.runs.B + (p.runs.r > 0)) / KC) + 2;  // tiles a run can touch
   const size_t slots = (size_t)p.runs.B * p.runs.seg;
   p.val_bytes = (slots * (32 * p.nb) * kStreamRows * sizeof(uint16_t) + 255) / 256 * 256;
   p.ws_bytes = p.val_bytes + slots * 4 * sizeof(float);
@@ -561,6 +562,8 @@ static int lin_check(const char* who, const void* x, const void* weight, int32_t
   const LinPlan p = lin_plan(n_rows, in_dim, out_dim);
   OOO_REQUIRE(workspace && ws_bytes >= p.ws_bytes, OOO_ERR_CAPACITY, "%s: workspace of %zu bytes needed (got %zu)",
               who, p.ws_bytes, ws_bytes);
+  // the kernels count chunks in 32 bits; 2^31 of them are 32 TiB of weight
+  OOO_REQUIRE(p.chunks <= INT32_MAX, OOO_ERR_UNSUPPORTED, "%s: weight of %lld 16 KiB blocks", who, p.chunks);
   *plan = p;
   return OOO_OK;
 }

@@ -295,3 +295,20 @@ def test_attention_workspace_serves_every_smaller_trie(Hq, Hkv, D):
         assert last is None or all(a <= b for a, b in zip(last, sizes)), N
         last = sizes
     assert last[-1] <= ooo.lib().ooo_tree_attn_noalloc_scratch_bytes()
+
+
+def test_linear_workspace_of_the_largest_sizes():
+    """Sizes whose chunk count leaves 32 bits are answered, not a crash, and
+    a call with them is refused on the host."""
+    L = ooo.lib()
+    fake = ctypes.c_void_p(0x1000)
+    big = 2**31 - 1
+    for K, O in ((64, big), (8192, big - 127), (16384, big - 127), (16384, big), (big - 63, big)):
+        K -= K % 64
+        tiles, KC = -(-O // 128), K // 64
+        blocks = min(tiles * KC, 256)
+        slots = blocks * ((tiles * KC + blocks - 1) // blocks // KC + 2)
+        assert L.ooo_linear_workspace(1, K, O) == slots * 32 * 128 * 2 + slots * 16, (K, O)
+    need = L.ooo_linear_workspace(1, 16384, big)
+    assert L.ooo_linear(fake, fake, 1, 16384, big, 1, 0, fake, fake, need - 1, None) == ooo.ERR_CAPACITY
+    assert L.ooo_linear(fake, fake, 1, 16384, big, 1, 0, fake, fake, need, None) == ooo.ERR_UNSUPPORTED
