@@ -651,7 +651,10 @@ static int stream_k(const char* who, const void* x, const void* weight, int32_t 
 // 13.7; 40 nodes, K 4096: I 4352 25.5 / 21.0, I 12416 36.1 / 40.8; 128 nodes:
 // K 4096, I 4352 38.3 / 31.5, K 2048 21.8 / 25.7, K 5120, I 27648 102 / 142;
 // 256 nodes: K 4096, I 4352 58.8 / 46, K 5120, I 27648 184 / 190.
-static bool swiglu_direct(int n_rows, int in_dim, int inter) {
+// The direct kernel stores four outputs (8 bytes) at a time; an output that
+// is not aligned for it goes through stream-K, whose epilogue stores each.
+static bool swiglu_direct(int n_rows, int in_dim, int inter, const void* out) {
+  if (reinterpret_cast<uintptr_t>(out) % 8) return false;
   const long long KC = in_dim / 64, units = inter / 16, cus = device_cus();
   const int ahead = n_rows <= 32 ? 500 : n_rows <= 64 ? 700 : 900;  // 0.01 us
   return KC * (32 * cus - 15 * units) < ahead * cus;
@@ -687,7 +690,7 @@ extern "C" int ooo_linear(const void* x, const void* weight, int32_t n_rows, int
               "ooo_linear: the SwiGLU epilogue needs out_dim %% 256 == 0 (gate and up halves of whole tiles)");
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   LinPlan p{};
-  if (epilogue == OOO_EPI_SWIGLU_BF16 && swiglu_direct(n_rows, in_dim, out_dim / 2)) {
+  if (epilogue == OOO_EPI_SWIGLU_BF16 && swiglu_direct(n_rows, in_dim, out_dim / 2, out)) {
     const int rc = lin_check("ooo_linear", x, weight, n_rows, in_dim, out_dim, weight_layout, workspace, ws_bytes, &p);
     if (rc != OOO_OK) return rc;
     launch_swiglu(p.nb, weight_layout == OOO_W_PACKED, (const uint16_t*)x, (const uint16_t*)weight, n_rows, in_dim,

@@ -122,6 +122,24 @@ def test_linear_swiglu_paths(N, K, I, packed):
     assert (act[N] == 7.0).all()
 
 
+@pytest.mark.parametrize("offset", [1, 2, 3, 4])
+def test_linear_swiglu_output_alignment(offset):
+    """Outputs that start at any bf16 element: the same values as an aligned
+    output within the rounding, and nothing beside them written."""
+    print(f"case linear swiglu output offset {offset}", flush=True)
+    N, K, I = 33, 128, 2048
+    rs = np.random.default_rng(offset)
+    x, w = _bits(rs, (N, K)), _bits(rs, (2 * I, K), 1.0 / math.sqrt(K))
+    ws = torch.zeros(ooo.linear_workspace(N, K, 2 * I), dtype=torch.uint8, device=DEV)
+    buf = torch.full((N * I + 8,), 7.0, dtype=torch.bfloat16, device=DEV)
+    ooo.linear(_dev_bf16(x), ooo.linear_pack(_dev_bf16(w)), buf[offset:offset + N * I].view(N, I),
+               ooo.EPI_SWIGLU_BF16, ws)
+    ref = f64(x) @ f64(w).T
+    got = _host_f64(buf[offset:offset + N * I].view(N, I))
+    assert gh.row_rel_err(got, om.silu(ref[:, :I]) * ref[:, I:]) <= TOL
+    assert (buf[:offset] == 7.0).all() and (buf[offset + N * I:] == 7.0).all()
+
+
 @pytest.mark.parametrize("scale", [3e4, 0.0])
 def test_linear_partials_beyond_fp16_range(scale):
     """The stream-K partial sums pass through the workspace in fp16 with a
