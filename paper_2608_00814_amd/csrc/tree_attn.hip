@@ -47,6 +47,7 @@ namespace {
 
 constexpr int kTile = 64;         // keys per tile
 constexpr int kEarlyTiles = 16;   // longest runs whose second tile is requested up front
+constexpr int kOneBatch = 32;     // splits the merge loads at once
 constexpr int kMaxMaskWords = 16;  // ancestor-mask words per node (up to 1024 nodes)
 
 struct AttnArgs {
@@ -64,6 +65,7 @@ struct AttnArgs {
   float* part_ml;    // per partial row: log2 of the split's weight, exponent of its scale
   int splits, row_blocks, Mpad, tiles_prefix, tiles_total;
   int tps;           // key tiles per split (split s takes tiles [s tps, (s + 1) tps))
+  int all_from;      // key tiles from which more than kOneBatch splits are worth it
   uint32_t g_inv;    // ceil(2^32 / G) (0 for G = 1): row / G is one multiplication
   int rows_first;    // order of the work items (see the launch)
   const int* P_dev;  // null, or the prefix length in device memory (P bounds it)
@@ -88,6 +90,16 @@ __device__ __forceinline__ int row_node(int row, int G, uint32_t g_inv) {
 __device__ __forceinline__ int xcd_order(int b, int total) {
   const int x = b & 7;
   return x * (total >> 3) + min(x, total & 7) + (b >> 3);
+}
+
+// Splits that run at a prefix of `tiles` key tiles with the tree's: all of the
+// plan's, but for a device prefix far below the bound that the plan was made
+// for, where the merge's second batch would cost more than the shorter runs
+// give (the planner's prices).  At a bound of 40000 rows, one node x 4 heads on
+// one KV head (63 splits) takes 10.8 us at prefixes of 50 to 1500 rows and 12.5
+// at 4000; with all splits it took 13.7 and 15.2.
+__device__ __forceinline__ int live_splits(const AttnArgs& a, int tiles) {
+  return a.splits > kOneBatch && tiles < a.all_from ? kOneBatch : a.splits;
 }
 
 typedef short i16x4 __attribute__((ext_vector_type(4)));
@@ -215,7 +227,9 @@ __global__ __launch_bounds__(64 * RG * (SPLIT ? 2 : 1)) void tree_attn_bf16_kern
   // row's key ranges and its rounding do not depend on the row block.  The
   // last splits can be empty when there are fewer tiles than splits
   // (handled below).
-  const int tps = a.P_dev ? (tiles_total + a.splits - 1) / a.splits : a.tps;
+  const int live = live_splits(a, tiles_total);
+  if (s >= live) return;
+  const int tps = a.P_dev ? (tiles_total + live - 1) / live : a.tps;
   const int t_begin = s * tps;
   const int t_end = min(t_begin + tps, tiles_total);
   const int ntiles = t_end - t_begin;
@@ -809,7 +823,7 @@ __global__ __launch_bounds__(64 * RG * (SPLIT ? 2 : 1)) void tree_attn_bf16_kern
 // 9.96 against one 9.74 us.
 constexpr int kCombineWaves = 1;
 
-template <int D, int SMAX, int CH>
+template <int D, int S0, int S1>
 __global__ __launch_bounds__(64 * kCombineWaves) void tree_attn_combine_kernel(AttnArgs a) {
   constexpr int NP = D / 16;  // group pairs per lane
   const int lane = threadIdx.x & 63;
@@ -830,21 +844,21 @@ __global__ __launch_bounds__(64 * kCombineWaves) void tree_attn_combine_kernel(A
   const f32x2_t* pml = reinterpret_cast<const f32x2_t*>(a.part_ml) + (size_t)g * a.Mpad + r;
   float m = -INFINITY, den = 0.f;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int ch = 0; ch < CH; ++ch) {
+  const auto merge = [&](auto n_c, int first) OOO_INLINE {
+    constexpr int SMAX = decltype(n_c)::value;
     f32x2_t ml[SMAX];
     u32x4 o[SMAX];
 #pragma unroll
     for (int s = 0; s < SMAX; ++s) {  // splits past the count re-read the last one (weight zero below)
-      const int sc = min(ch * SMAX + s, a.splits - 1);
+      const int sc = min(first + s, a.splits - 1);
       ml[s] = pml[sc * split_ml];
       o[s] = po[sc * split_o];
     }
     const float m_old = m;
 #pragma unroll
-    for (int s = 0; s < SMAX; ++s) m = ch * SMAX + s < a.splits ? __builtin_fmaxf(m, ml[s][0]) : m;
+    for (int s = 0; s < SMAX; ++s) m = first + s < a.splits ? __builtin_fmaxf(m, ml[s][0]) : m;
     const float base = m == -INFINITY ? 0.f : m;
-    if (ch > 0) {
+    if (first > 0) {
       const float alpha = __builtin_amdgcn_exp2f(m_old - base);
       den *= alpha;
 #pragma unroll
@@ -852,7 +866,7 @@ __global__ __launch_bounds__(64 * kCombineWaves) void tree_attn_combine_kernel(A
     }
 #pragma unroll
     for (int s = 0; s < SMAX; ++s) {
-      const float wgt = ch * SMAX + s < a.splits ? __builtin_amdgcn_exp2f(ml[s][0] - base) : 0.f;
+      const float wgt = first + s < a.splits ? __builtin_amdgcn_exp2f(ml[s][0] - base) : 0.f;
       den += wgt;
       const float wv2 = __builtin_amdgcn_ldexpf(wgt, (int)ml[s][1]);
 #pragma unroll
@@ -862,6 +876,12 @@ __global__ __launch_bounds__(64 * kCombineWaves) void tree_attn_combine_kernel(A
         acc[2 * e + 1] += wv2 * h[1];
       }
     }
+  };
+  merge(std::integral_constant<int, S0>{}, 0);
+  if constexpr (S1 > 0) {
+    const int P = a.P_dev ? min(max(*a.P_dev, 0), a.P) : a.P;
+    if (live_splits(a, (P + kTile - 1) / kTile + (a.N + kTile - 1) / kTile) > S0)
+      merge(std::integral_constant<int, S1>{}, S0);
   }
   const float inv = 1.f / den;
   const int node = row_node(r, a.G, a.g_inv), head = g * a.G + (r - node * a.G);
@@ -1076,10 +1096,11 @@ __global__ __launch_bounds__(64 * 1024 / D) void tree_attn_f32_kernel(const floa
 
 // The combine kernel loads exactly the splits there are (up to 16; more in
 // groups of 4): each padding slot is one more load per lane, and the merge
-// is bound by its loads.  More than 32 splits are merged in two batches.
-template <int D, int S, int CH = 1>
+// is bound by its loads.  More than 32 splits are merged in two batches, the
+// second only where they all run (live_splits).
+template <int D, int S, int S1 = 0>
 void launch_combine_n(dim3 grid, hipStream_t st, const AttnArgs& a) {
-  tree_attn_combine_kernel<D, S, CH><<<grid, 64 * kCombineWaves, 0, st>>>(a);
+  tree_attn_combine_kernel<D, S, S1><<<grid, 64 * kCombineWaves, 0, st>>>(a);
 }
 template <int D>
 void launch_combine(int splits, dim3 grid, hipStream_t st, const AttnArgs& a) {
@@ -1104,13 +1125,13 @@ void launch_combine(int splits, dim3 grid, hipStream_t st, const AttnArgs& a) {
       if (splits <= 24) return launch_combine_n<D, 24>(grid, st, a);
       if (splits <= 28) return launch_combine_n<D, 28>(grid, st, a);
       if (splits <= 32) return launch_combine_n<D, 32>(grid, st, a);
-      if (splits <= 48) return launch_combine_n<D, 24, 2>(grid, st, a);
-      return launch_combine_n<D, 32, 2>(grid, st, a);
+      if (splits <= 48) return launch_combine_n<D, kOneBatch, 16>(grid, st, a);
+      return launch_combine_n<D, kOneBatch, 32>(grid, st, a);
   }
 }
 
 struct Plan {
-  int waves, row_blocks, Mpad, tiles_prefix, tiles_total, splits, tps;
+  int waves, row_blocks, Mpad, tiles_prefix, tiles_total, splits, tps, all_from;
   size_t ws_bytes;    // the query's answer
   size_t call_bytes;  // what a call checks for: 0 where this trie is too wide to split
 };
@@ -1147,7 +1168,7 @@ Plan make_plan(int N, int Hq, int Hkv, int D, int P, ooo_dtype dt, int force_spl
   int splits = 1, best = INT32_MAX;
   for (int sc = 1; sc <= max_splits && sc <= p.tiles_total && sc <= 64; ++sc) {
     const int cost = 20 * ((p.tiles_total + sc - 1) / sc) + split_cost * sc + (sc > 1 ? merge_cost : 0) +
-                     (sc > 32 ? 40 : 0);
+                     (sc > kOneBatch ? 40 : 0);
     if (cost < best) best = cost, splits = sc;
   }
   if (force_splits > 0) splits = force_splits < 32 ? force_splits : 32;
@@ -1156,6 +1177,12 @@ Plan make_plan(int N, int Hq, int Hkv, int D, int P, ooo_dtype dt, int force_spl
   // fixed-size runs of tiles; the last run may be shorter
   p.tps = (p.tiles_total + splits - 1) / splits;
   p.splits = (p.tiles_total + p.tps - 1) / p.tps;
+  if (p.splits > kOneBatch) {
+    // 20 tiles (1 / 32 - 1 / splits) > the second batch and the splits past 32
+    const long long extra = p.splits - kOneBatch;
+    const int from = (int)((40 + split_cost * extra) * kOneBatch * p.splits / (20 * extra)) + 1;
+    p.all_from = from < p.tiles_total ? from : p.tiles_total;
+  }
   // Scratch.  A plan that splits never has more blocks than CUs, nor more
   // splits than 64 or than there are tiles; the query counts the blocks of a
   // KV head that these bounds allow, which no smaller trie and no shorter
@@ -1260,6 +1287,7 @@ extern "C" int ooo_tree_attn_ex(const void* q, const void* k_cache, const void* 
     a.tiles_prefix = p.tiles_prefix;
     a.tiles_total = p.tiles_total;
     a.tps = p.tps;
+    a.all_from = p.all_from;
     // With fewer KV heads than XCDs a head's work spreads over several.  Over
     // long runs of tiles an XCD then takes all row blocks of some splits, so
     // that K and V come into one L2 instead of each; over short ones all

@@ -84,6 +84,34 @@ def test_attention_device_prefix(P, bound, N, Hq, Hkv):
     assert gh.row_rel_err(got.reshape(N * Hq, D), ref.reshape(N * Hq, D)) <= TOL
 
 
+# (P, bound, N, Hq, Hkv, D): bounds whose plan has more than 32 splits, at
+# prefixes that leave most of them empty, that run 32 (1 to 10 tiles each), that
+# run all, and at the bound; and plans whose row blocks go inside the splits
+# (fewer than 8 KV heads, runs of 8 tiles and more) over runs shorter than that
+@pytest.mark.parametrize("P,bound,N,Hq,Hkv,D", [
+    (0, 40000, 2, 4, 1, 128), (1000, 40000, 2, 4, 1, 128), (20000, 40000, 2, 4, 1, 128), (23000, 40000, 2, 4, 1, 128),
+    (40000, 40000, 2, 4, 1, 128), (10, 40000, 2, 6, 6, 64), (9000, 40000, 2, 6, 6, 64), (39990, 40000, 2, 6, 6, 64),
+    (70, 20000, 150, 4, 2, 128), (5000, 20000, 150, 4, 2, 128), (19999, 20000, 150, 4, 2, 64),
+])
+def test_attention_device_prefix_of_long_bounds(P, bound, N, Hq, Hkv, D):
+    print(f"case attention device prefix of a long bound P={P} bound={bound} N={N} Hq={Hq} Hkv={Hkv} D={D}", flush=True)
+    rs = np.random.default_rng(P + N)
+    cap = P + N  # as many rows as the prefix needs; the strides of the bound's cache
+    parent = np.array([-1] + [int(rs.integers(0, i)) for i in range(1, N)], np.int32)
+    W = (N + 63) // 64
+    md = torch.from_numpy(ov.ancestor_masks(parent, W).view(np.int64)).to(DEV).view(N, W)
+    q, k, v = (wl.to_bf16_bits(rs.normal(size=s).astype(np.float32)) for s in ((N, Hq, D), (Hkv, cap, D), (Hkv, cap, D)))
+    kd, vd = (torch.full((Hkv, bound + N, D), float("nan"), dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    kd[:, :cap], vd[:, :cap] = gh.to_dev(k, "bf16", DEV), gh.to_dev(v, "bf16", DEV)
+    ws = torch.full((ooo.tree_attn_workspace(N, Hq, Hkv, D, bound, ooo.BF16) // 4,), float("nan"), device=DEV)
+    out = torch.full((N, Hq, D), float("nan"), dtype=torch.bfloat16, device=DEV)
+    ooo.tree_attn(gh.to_dev(q, "bf16", DEV), kd, vd, bound, N, md, Hq, Hkv, 1.0 / math.sqrt(D), out, ws,
+                  prefix_dev=_prefix_dev(P))
+    ref = ov.tree_attention(f64(q), f64(k), f64(v), P, parent, Hkv)
+    got = f64(gh.to_host(out, "bf16"))
+    assert gh.row_rel_err(got.reshape(N * Hq, D), ref.reshape(N * Hq, D)) <= TOL
+
+
 def test_rotation_and_compaction_device_prefix():
     print("case qk_norm_rope and kv_compact with a device prefix", flush=True)
     rs = np.random.default_rng(9)

@@ -258,6 +258,41 @@ def test_attention_plan_edges(case):
     assert gh.row_rel_err(got, ref) <= gh.ATTN_TOL
 
 
+# (P, N, G, Hkv, D, splits): plans of more than 32 splits (256 compute units):
+# the merge's second batch of 16 at its least, inside and full, and of 32
+MANY_SPLITS = [
+    (40000, 2, 1, 6, 64, 42),
+    (30000, 2, 1, 5, 128, 47),
+    (30600, 2, 1, 5, 128, 48),
+    (30500, 70, 1, 5, 64, 48),
+    (31200, 2, 1, 5, 128, 49),
+    (38000, 3, 1, 5, 64, 50),
+    (27500, 2, 3, 6, 128, 40),
+]
+
+
+@pytest.mark.parametrize("case", MANY_SPLITS, ids=[f"P{c[0]}-N{c[1]}-G{c[2]}-Hkv{c[3]}-D{c[4]}-S{c[5]}"
+                                                   for c in MANY_SPLITS])
+def test_attention_many_splits(case):
+    P, N, G, Hkv, D, S = case
+    print(f"case attention many splits {case}", flush=True)
+    rs, q, k, v, cap = _attn_inputs(P, N, G, Hkv, D, "bf16", seed=P + N)
+    t = _trie("chain" if N < 4 else "random", N, rs)
+    mask = ov.ancestor_masks(t["parent"], (N + 63) // 64)
+    qd, kd, vd = (gh.to_dev(a, "bf16", DEV) for a in (q, k, v))
+    md = torch.from_numpy(mask.view(np.int64)).to(DEV)
+    out = torch.full((N, G * Hkv, D), float("nan"), dtype=torch.bfloat16, device=DEV)
+    ws = torch.full((ooo.tree_attn_workspace(N, G * Hkv, Hkv, D, P, ooo.BF16) // 4,), float("nan"), device=DEV)
+    ooo.tree_attn(qd, kd, vd, P, N, md, G * Hkv, Hkv, 1.0 / math.sqrt(D), out, ws)
+    ref = ov.tree_attention(wl.to_f64(q, "bf16"), wl.to_f64(k, "bf16"), wl.to_f64(v, "bf16"), P, t["parent"], Hkv)
+    assert gh.row_rel_err(gh.wl.to_f64(gh.to_host(out, "bf16"), "bf16"), ref) <= gh.ATTN_TOL
+    # the splits that ran: their weights follow S partial blocks in the workspace
+    M, rows = N * G, 64 if N * G <= 64 else 128
+    rows *= -(-M // rows)
+    ml = ws[S * Hkv * rows * D // 2:][:S * Hkv * rows * 2].view(S, Hkv, rows, 2)
+    assert torch.isfinite(ml[:, :, :M]).all() and torch.isnan(ws[S * Hkv * rows * (D // 2 + 2):]).all()
+
+
 # (P, N, G, Hkv, D): edges of the float32 kernel's 16-row blocks and 16-key
 # tiles: no prefix, one row, a full tile and one key more, several mask words,
 # more waves than tiles, G that does not divide a block
