@@ -104,7 +104,7 @@ inline Runs cut_runs(long long C, int B, int KC, bool spread) {
 template <int NB, bool PACKED>
 __global__ __launch_bounds__(kTallThreads) void linear_bf16_kernel(const uint16_t* __restrict__ X,
                                                                    const uint16_t* __restrict__ Wt, int N, int K,
-                                                                   int O, Runs runs, Partials part) {
+                                                                   int O, Runs runs, Ring ring, Partials part) {
   constexpr int NPAD = 32 * NB;
   __shared__ __attribute__((aligned(1024))) uint8_t lds[kRingBytes];
   const int lane = threadIdx.x & 63;
@@ -116,7 +116,6 @@ __global__ __launch_bounds__(kTallThreads) void linear_bf16_kernel(const uint16_
   const int total = runs.lo(b + 1) - lo;  // chunks of this block (>= 1: B <= C)
   const int first_tile = (int)((unsigned)lo / (unsigned)KC), kc0 = lo - first_tile * KC;
   const auto tile = [&](int t) { return GroupRange{4 * t, min(4 * t + 4, groups)}; };
-  const Ring ring(min(4, groups), N, NB);
 
   if (wave >= 4) {
     const int ld = wave - 4;
@@ -226,24 +225,21 @@ struct PairSlots {
 template <int NB, int RG, bool PACKED>
 __global__ __launch_bounds__(kTallThreads) void linear_swiglu_kernel(const uint16_t* __restrict__ X,
                                                                      const uint16_t* __restrict__ Wt, int N, int K,
-                                                                     int inter, uint16_t* __restrict__ out) {
-  constexpr int SLOTS = 4 * RG;
+                                                                     int inter, Deal deal, Ring ring,
+                                                                     uint16_t* __restrict__ out) {
   __shared__ __attribute__((aligned(1024))) uint8_t lds[kRingBytes];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int KC = K / 64;
-  const int units = inter / 16, grid = (int)gridDim.x, b = (int)blockIdx.x;  // grid <= units
-  const int T = (units + SLOTS * grid - 1) / (SLOTS * grid);
-  const int per = units / (T * grid), more = units % (T * grid);
-  const auto first = [&](int i) { return per * i + min(i, more); };  // first unit of tile i of T * grid
-  const auto tile = [&](int t) { return GroupRange{first(b + t * grid), first(b + t * grid + 1)}; };
-  const Ring ring(per + (more > 0), N, NB);
+  const int grid = (int)gridDim.x, b = (int)blockIdx.x;
+  const int T = deal.T;
+  const auto tile = [&](int t) { return GroupRange{deal.first(b + t * grid), deal.first(b + t * grid + 1)}; };
 
   if (wave >= 4) {
     const int ld = wave - 4;
     XShare<NB> xs(X, N, K, ld, lane);
     PairSlots<RG, PACKED> slots(Wt, KC, K, inter, lane);
-    tall_load<NB, RG>(0, 0, T * KC, KC, per, ld, tile, slots, xs, ring, lds);
+    tall_load<NB, RG>(0, 0, T * KC, KC, deal.per, ld, tile, slots, xs, ring, lds);
     return;
   }
 
@@ -624,12 +620,16 @@ static int stream_k(const char* who, const void* x, const void* weight, int32_t 
   const uint16_t* W = (const uint16_t*)weight;
   const Partials part = partials_in(workspace, p);
   const bool pk = weight_layout == OOO_W_PACKED;
-#define OOO_LIN_LAUNCH(NBV)                                                                                           \
-  do {                                                                                                               \
-    if (pk)                                                                                                          \
-      linear_bf16_kernel<NBV, true><<<p.runs.B, kTallThreads, 0, st>>>(X, W, n_rows, in_dim, out_dim, p.runs, part); \
-    else                                                                                                             \
-      linear_bf16_kernel<NBV, false><<<p.runs.B, kTallThreads, 0, st>>>(X, W, n_rows, in_dim, out_dim, p.runs, part); \
+  const int groups = (out_dim + 31) / 32;
+  const Ring ring = make_ring(groups < 4 ? groups : 4, n_rows, p.nb);
+#define OOO_LIN_LAUNCH(NBV)                                                                                            \
+  do {                                                                                                                \
+    if (pk)                                                                                                           \
+      linear_bf16_kernel<NBV, true><<<p.runs.B, kTallThreads, 0, st>>>(X, W, n_rows, in_dim, out_dim, p.runs, ring,    \
+                                                                       part);                                         \
+    else                                                                                                              \
+      linear_bf16_kernel<NBV, false><<<p.runs.B, kTallThreads, 0, st>>>(X, W, n_rows, in_dim, out_dim, p.runs, ring,   \
+                                                                        part);                                        \
   } while (0)
   if (p.nb == 1) OOO_LIN_LAUNCH(1);
   else if (p.nb == 2) OOO_LIN_LAUNCH(2);
@@ -665,10 +665,12 @@ static void launch_swiglu(int nb, bool pk, const uint16_t* X, const uint16_t* W,
   const int units = inter / 16;
   const int blocks = units < device_cus() ? units : device_cus();
   const bool tall = (units + blocks - 1) / blocks > 4;
-#define OOO_SW_LAUNCH(NBV, RGV)                                                                         \
-  do {                                                                                                 \
-    if (pk) linear_swiglu_kernel<NBV, RGV, true><<<blocks, kTallThreads, 0, st>>>(X, W, N, K, inter, out);  \
-    else linear_swiglu_kernel<NBV, RGV, false><<<blocks, kTallThreads, 0, st>>>(X, W, N, K, inter, out);    \
+  const Deal deal = make_deal(units, blocks, tall && nb < 8 ? 2 : 1);
+  const Ring ring = make_ring(deal.slots(), N, nb);
+#define OOO_SW_LAUNCH(NBV, RGV)                                                                                  \
+  do {                                                                                                          \
+    if (pk) linear_swiglu_kernel<NBV, RGV, true><<<blocks, kTallThreads, 0, st>>>(X, W, N, K, inter, deal, ring, out); \
+    else linear_swiglu_kernel<NBV, RGV, false><<<blocks, kTallThreads, 0, st>>>(X, W, N, K, inter, deal, ring, out);   \
   } while (0)
   if (nb == 1 && tall) OOO_SW_LAUNCH(1, 2);
   else if (nb == 1) OOO_SW_LAUNCH(1, 1);

@@ -48,28 +48,22 @@ constexpr int kLmRows = kStreamRows;  // vocabulary rows per tile (4 waves x 32)
 template <int NB, int RG, bool PACKED>
 __global__ __launch_bounds__(kTallThreads) void lmhead_bf16_kernel(const uint16_t* __restrict__ X,
                                                                    const uint16_t* __restrict__ Wt, int N, int H,
-                                                                   int V, Cand* __restrict__ partial,
+                                                                   int V, Deal deal, Ring ring,
+                                                                   Cand* __restrict__ partial,
                                                                    float* __restrict__ logits) {
-  constexpr int SLOTS = 4 * RG;
   __shared__ __attribute__((aligned(1024))) uint8_t lds[kRingBytes];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int chunks = H / 64;
   const int b = (int)blockIdx.x, grid = (int)gridDim.x;
-  const int groups = (V + 31) / 32;
-  // Tiles of `per` or per + 1 groups, T a block: block b takes tiles b, b +
-  // grid, ..., so that at any time the blocks read neighbouring rows.
-  const int T = (groups + SLOTS * grid - 1) / (SLOTS * grid);
-  const int per = groups / (T * grid), more = groups % (T * grid);
-  const auto first = [&](int i) { return per * i + min(i, more); };  // first group of tile i of T * grid
-  const auto tile = [&](int t) { return GroupRange{first(b + t * grid), first(b + t * grid + 1)}; };
-  const Ring ring(per + (more > 0), N, NB);
+  const int T = deal.T;
+  const auto tile = [&](int t) { return GroupRange{deal.first(b + t * grid), deal.first(b + t * grid + 1)}; };
 
   if (wave >= 4) {
     const int ld = wave - 4;
     XShare<NB> xs(X, N, H, ld, lane);
     GroupSlots<RG, PACKED> slots(Wt, chunks, V, H, lane);
-    tall_load<NB, RG>(0, 0, T * chunks, chunks, per, ld, tile, slots, xs, ring, lds);
+    tall_load<NB, RG>(0, 0, T * chunks, chunks, deal.per, ld, tile, slots, xs, ring, lds);
     __syncthreads();  // matches the compute waves' barriers around the final reduction
     __syncthreads();
     return;
@@ -391,12 +385,17 @@ extern "C" int ooo_lmhead_argmax(const void* hidden, const void* weight, int32_t
     const uint16_t* X = (const uint16_t*)hidden;
     const uint16_t* W = (const uint16_t*)weight;
     const bool pk = weight_layout == OOO_W_PACKED;
-#define OOO_LM_LAUNCH(NBV, RGV)                                                                                        \
-  do {                                                                                                                \
-    if (pk)                                                                                                           \
-      lmhead_bf16_kernel<NBV, RGV, true><<<p.blocks, kTallThreads, 0, st>>>(X, W, n_nodes, hidden_dim, vocab, part, logits); \
-    else                                                                                                              \
-      lmhead_bf16_kernel<NBV, RGV, false><<<p.blocks, kTallThreads, 0, st>>>(X, W, n_nodes, hidden_dim, vocab, part, logits); \
+    const int rg = p.nb == 8 ? 1 : 2;
+    const Deal deal = make_deal((vocab + 31) / 32, p.blocks, rg);
+    const Ring ring = make_ring(deal.slots(), n_nodes, p.nb);
+#define OOO_LM_LAUNCH(NBV, RGV)                                                                                       \
+  do {                                                                                                               \
+    if (pk)                                                                                                          \
+      lmhead_bf16_kernel<NBV, RGV, true><<<p.blocks, kTallThreads, 0, st>>>(X, W, n_nodes, hidden_dim, vocab, deal,   \
+                                                                            ring, part, logits);                     \
+    else                                                                                                             \
+      lmhead_bf16_kernel<NBV, RGV, false><<<p.blocks, kTallThreads, 0, st>>>(X, W, n_nodes, hidden_dim, vocab, deal,  \
+                                                                             ring, part, logits);                    \
   } while (0)
     if (p.nb == 1) OOO_LM_LAUNCH(1, 2);
     else if (p.nb == 2) OOO_LM_LAUNCH(2, 2);
