@@ -13,10 +13,10 @@
 //    in each half read eight different pieces, all 64 banks once.  (An XOR
 //    by r % 8 gave rows r and r + 8 the same banks: a 2-way conflict on
 //    every fragment read.)
-//  * Seven waves per block: four compute waves own 32 W rows each; two
-//    loader waves DMA the W slots (two each) and a third the X chunk into a
-//    ring of NS stages, NS - 1 chunks requested ahead of the one consumed.
-//    Wider node tiles need more X bytes per stage, so fewer stages fit.
+//  * Eight waves per block: four compute waves own the 32-row slots (one or
+//    two each); four loader waves copy a share of the W slots and of the X
+//    rows each into a ring whose depth follows from the bytes of a stage
+//    (make_ring), all but one stage requested ahead of the one consumed.
 //  * The contraction index inside a chunk follows the pieces: MFMA k-step s,
 //    lane half u, element e is k = 8 (2s + u) + e for both operands.
 #pragma once
@@ -26,7 +26,6 @@
 namespace ooo {
 
 constexpr int kStreamRows = 128;  // W rows per tile (4 compute waves x 32)
-constexpr int kStreamThreads = 448;  // 4 compute waves + 2 W loaders + 1 X loader
 
 // physical piece of logical piece p in LDS row r (and in the packed layout)
 __device__ __forceinline__ int piece_swz(int r) { return (r >> 1) & 7; }
