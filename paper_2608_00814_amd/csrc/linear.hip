@@ -642,22 +642,28 @@ static int stream_k(const char* who, const void* x, const void* weight, int32_t 
 
 // Whether the SwiGLU projection owns whole columns per block or goes through
 // stream-K.  With u units per CU a block of the direct kernel takes about
-// 3 + KC max(0.32, 0.15 u) us (below two units a CU the chunk pipeline's own
-// period binds, not the bytes) and stream-K with its second kernel about
-// 8 + 0.15 KC u (10 at 33-64 nodes, 12 past that), so stream-K is only ahead
-// for few units under a long K.  Measured, direct / stream-K us: one node,
-// K 4096: I 4352 (u 1.06) 23.1 / 18.3, I 8320 26.1 / 28.1, I 12416 37.2 /
-// 38.4, I 14336 39.6 / 43.2; K 1024, I 3072 8.0 / 9.8; K 2048, I 4352 13.3 /
-// 13.7; 40 nodes, K 4096: I 4352 25.5 / 21.0, I 12416 36.1 / 40.8; 128 nodes:
-// K 4096, I 4352 38.3 / 31.5, K 2048 21.8 / 25.7, K 5120, I 27648 102 / 142;
-// 256 nodes: K 4096, I 4352 58.8 / 46, K 5120, I 27648 184 / 190.
+// KC max(flat, slope u), where below one or two units a CU the chunk
+// pipeline's own period binds (flat) and not the bytes, and stream-K with its
+// second kernel KC slope u + ahead: so stream-K is ahead for few units under a
+// long K.  The prices (0.01 us) are fitted to both kernels at 14 shapes (K 1024
+// to 8192, I 2176 to 27648; weights read from HBM each call) and 7 row counts;
+// the choice is the better one, within 1 %, at each.  Direct / stream-K us at
+// 1, 64, 128 and 256 rows: K 4096, I 4352 (u 1.06) 19.1 / 18.8, 22.5 / 22.1,
+// 34.7 / 30.0, 51.8 / 43.9; I 6016 (1.47) 20.4 / 22.9, 26.5 / 26.9, 37.1 /
+// 35.7, 52.7 / 51.1; I 12416 (3.03) 37.0 / 39.3, 39.2 / 45.3, 48.6 / 59.0,
+// 75.2 / 79.8; K 8192, I 4352 36.1 / 29.2, 45.1 / 33.7, 65.9 / 44.5, 97.0 /
+// 62.2; I 7168 (1.75) 48.9 / 42.9, 50.6 / 48.8, 67.9 / 60.4, 102.1 / 84.9; K
+// 1024, I 3072 (0.75) 6.8 / 9.6, 7.7 / 12.8, 10.6 / 18.0, 16.5 / 29.8.
 // The direct kernel stores four outputs (8 bytes) at a time; an output that
 // is not aligned for it goes through stream-K, whose epilogue stores each.
 static bool swiglu_direct(int n_rows, int in_dim, int inter, const void* out) {
   if (reinterpret_cast<uintptr_t>(out) % 8) return false;
+  struct Price {
+    int flat, slope, ahead;
+  };
+  const Price p = n_rows <= 64 ? Price{30, 13, 800} : n_rows <= 128 ? Price{49, 22, 1000} : Price{78, 29, 2000};
   const long long KC = in_dim / 64, units = inter / 16, cus = device_cus();
-  const int ahead = n_rows <= 32 ? 500 : n_rows <= 64 ? 700 : 900;  // 0.01 us
-  return KC * (32 * cus - 15 * units) < ahead * cus;
+  return KC * (p.flat * cus - p.slope * units) < p.ahead * cus;
 }
 
 static void launch_swiglu(int nb, bool pk, const uint16_t* X, const uint16_t* W, int N, int K, int inter, uint16_t* out,
