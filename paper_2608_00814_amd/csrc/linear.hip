@@ -9,7 +9,7 @@
 //    head's layout, ooo_linear_pack); the work is the sequence of (128-row
 //    tile, 64-column chunk) blocks in tile-major order.
 //  * Stream-K: a persistent grid (one block per CU) where block b takes a
-//    contiguous run of chunks, C / B of them or one more.  Every block
+//    contiguous run of chunks, C / B of them or one more (Runs).  Every block
 //    streams the same bytes whatever O and K are; a run covers the end of
 //    one tile and the start of the next.
 //  * Inside a block, the LM head's streaming core (stream_core.h) with
@@ -34,8 +34,8 @@
 //    (linear_swiglu_kernel).
 // Two layers at the Qwen3-8B shape (graph replay), with 128-row tiles of
 // seven waves, padded X and partial rows, slot lists in LDS and SwiGLU
-// through stream-K against this: 242.6 -> 202.5 us at one node, 281.1 ->
-// 238.2 at 64; one layer at H 5120, I 27648, 128 nodes 317.2 -> 275.3.
+// through stream-K against this: 243.3 -> 196.9 us at one node, 282.9 ->
+// 231.4 at 64; one layer at H 5120, I 27648, 128 nodes 314.9 -> 259.2.
 #include <math.h>
 
 #include "device_common.h"
@@ -297,8 +297,7 @@ __device__ __forceinline__ TileSlots tile_slots(const Runs& runs, int KC, int t)
 }
 
 // Sum of the partials at (node n, tile row r): element e = n * 128 + r, in block
-// order whichever kernel adds them (the same
-// rounding).  The loads of a batch of S slots (S = 4, 8 or 16, the smallest
+// order whichever kernel adds them (the same rounding).  The loads of a batch of S slots (S = 4, 8 or 16, the smallest
 // that holds the list; longer lists take several batches) are all issued
 // before the first add, so a sum costs one round trip to memory; slots past
 // the end of the list re-read the last one and are not added.
@@ -573,9 +572,12 @@ extern "C" size_t ooo_linear_workspace(int32_t n_rows, int32_t in_dim, int32_t o
   return lin_plan(n_rows, in_dim, out_dim).ws_bytes;
 }
 
-// The fused epilogues refuse shapes with more than 64 stream-K runs on one
-// 128-row tile when the chunks are cut at C b / B (very few tiles under a
-// long K).  Only then can a tile be that wide, so the count is taken there.
+// The fused epilogues refuse shapes whose chunks, cut at C b / B on at most
+// 256 blocks, put more than 64 runs on one 128-row tile (very few tiles under
+// a long K: 256 columns under K 8192).  Only the entry points' contract asks
+// for it: earlier epilogues kept a tile's runs in lists of 64, these take any
+// number in batches of 16, and the count is of that cut, whichever the kernels
+// use, so that the same shapes are refused as ever.
 constexpr int kMaxTileRuns = 64;
 static bool too_many_runs(int n_rows, int in_dim, int out_dim) {
   if (n_rows < 1 || in_dim < 64 || in_dim % 64 || n_rows > 256 || out_dim < 1) return false;  // refused elsewhere

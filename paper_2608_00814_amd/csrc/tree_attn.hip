@@ -12,8 +12,10 @@
 //    A split is a fixed-length run of tiles, so the key ranges a row's
 //    partial sums cover (and its rounding) do not depend on the row block:
 //    for a given key layout a node's output is bitwise the same in tries of
-//    any size that get the same split count (the count depends on the trie
-//    size only where the CUs limit it).
+//    any size that get the same split count.  The count depends on the trie
+//    size through the CUs that its row blocks leave, and through the planner's
+//    prices, which change at 32 query rows per KV head (the merge) and, for
+//    head_dim 64, at 64 (a split).
 //  * Scores are computed transposed, S^T = K Q^T, and the output as
 //    O^T = V^T P^T.  With the A-operand rows of K permuted (bits 2 and 3 of
 //    the row index swapped) every lane ends up holding one query row: its
@@ -30,9 +32,11 @@
 //    the split's log2 weight and the power's exponent, 8 bytes per row)
 //    that a second kernel combines, loading exactly the splits there are;
 //    with one split the kernel writes O directly.
-//  * Launch order is XCD-aware: consecutive work items (same KV head and
-//    row block, neighbouring splits) go to blocks that share blockIdx % 8,
-//    so one head's K/V stream stays in one XCD's L2.
+//  * Launch order is XCD-aware: consecutive work items go to blocks that
+//    share blockIdx % 8, one XCD: neighbouring splits of a KV head's row block,
+//    so that one head's K/V stream stays in one L2, or, with fewer KV heads
+//    than XCDs and long runs of tiles, the row blocks of one split (the rule
+//    and its measurements stand at the launch).
 #include <math.h>
 #include <stdlib.h>
 
@@ -911,11 +915,11 @@ __global__ __launch_bounds__(64 * kCombineWaves) void tree_attn_combine_kernel(A
 // small sizes and by the matrix rate at large ones.  A block per
 // (node, query head) with one thread per key, the earlier form, read every
 // key row once per query head in 16-byte pieces of 64 different rows: 64 nodes
-// x 16 heads over 4 KV heads of 128 at prefix 1024 took 153 us and now takes
-// 33, 25 nodes x 4 heads of 64 at 128 10.7 and 8.0, one node at 128 9.7 and
-// 6.8.  Error against 64 bits at these three: 2.7e-7 -> 1.8e-7, 1.7e-7 ->
-// 1.5e-7, 1.9e-7 -> 1.6e-7 (means over 12 seeds): products are added in chains
-// of eight and the chains in trees.
+// x 16 heads over 4 KV heads of 128 at prefix 1024 took 151 us and now takes
+// 33, 25 nodes x 4 heads of 64 at 128 10.7 and 7.8, one node at 128 9.7 and
+// 6.3.  Error against 64 bits of that form and this at these three: 2.7e-7
+// and 1.8e-7, 1.7e-7 and 1.5e-7, 1.9e-7 and 1.6e-7 (means over 12 seeds):
+// products are added in chains of eight and the chains in trees.
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // dword-aligned
 template <int D>
 __global__ __launch_bounds__(64 * 1024 / D) void tree_attn_f32_kernel(const float* q, const float* k, const float* v,
@@ -1158,10 +1162,10 @@ Plan make_plan(int N, int Hq, int Hkv, int D, int P, ooo_dtype dt, int force_spl
   // work it takes off the blocks, 1 us for few rows, 2 us more where more than
   // 32 splits take a second batch of loads (units of 0.05 us; fitted to graphs
   // of calls over 196 shapes: 1 to 256 nodes, prefixes 40 to 16384, 1 to 8 KV
-  // heads, head_dim 64 and 128, and every split count).  The earlier 1.3 us per tile and 0.25 to 0.5 us per
-  // split chose too few splits where the blocks do not fill the chip: 100
-  // nodes x 8 heads of 64 at prefix 1024 took 9.6 us with 6 splits and
-  // 7.9 us with 18.
+  // heads, head_dim 64 and 128, and every split count).  The earlier 1.3 us
+  // per tile and 0.25 to 0.5 us per split chose too few splits where the
+  // blocks do not fill the chip: 100 nodes x 8 heads of 64 at prefix 1024 took
+  // 9.6 us with 6 splits and 7.9 us with 18.
   // Up to 64 splits: one node x 4 heads on one KV head at prefix 40000 took
   // 29.3 us with 32 (20 tiles each) and takes 23.0 with 63; at 16384 (9 tiles)
   // more than 32 lose as often as they gain.
@@ -1295,9 +1299,12 @@ extern "C" int ooo_tree_attn_ex(const void* q, const void* k_cache, const void* 
     // long runs of tiles an XCD then takes all row blocks of some splits, so
     // that K and V come into one L2 instead of each; over short ones all
     // splits of some row blocks, whose partials its combine blocks re-read.
-    // 256 nodes x 4 heads on one KV head at prefix 40000 39.6 -> 32.7 us per
-    // call, 100 x 14 on 2 at 16384 (13 tiles a split) 25.4 -> 24.2, but at
-    // 1024 (2 tiles) 11.4 -> 12.6.
+    // Time of the second order over the first, geometric means over 264 shapes
+    // (33 to 256 nodes, 1 to 4 KV heads, prefixes 2000 to 40000): 1.00 at runs
+    // of 2 tiles, 1.01 to 1.03 at 3 to 6, 1.00 at 7, 1.02 at 8, 1.02 to 1.04 at
+    // 10 to 13 and 1.05 from 20 on (up to 1.19); single shapes scatter by 6 %
+    // to either side below 8 tiles.  256 nodes x 4 heads on one KV head at
+    // prefix 40000: 39.6 -> 32.7 us per call.
     a.rows_first = n_kv_heads < 8 && p.tps >= 8;
     const auto inverse = [](int n) { return n > 1 ? (uint32_t)(((1ull << 32) + n - 1) / n) : 0u; };
     a.g_inv = inverse(G);
