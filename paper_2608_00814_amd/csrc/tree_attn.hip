@@ -1301,9 +1301,9 @@ extern "C" int ooo_tree_attn_ex(const void* q, const void* k_cache, const void* 
     // splits of some row blocks, whose partials its combine blocks re-read.
     // Time of the second order over the first, geometric means over 264 shapes
     // (33 to 256 nodes, 1 to 4 KV heads, prefixes 2000 to 40000): 1.00 at runs
-    // of 2 tiles, 1.01 to 1.03 at 3 to 6, 1.00 at 7, 1.02 at 8, 1.02 to 1.04 at
-    // 10 to 13 and 1.05 from 20 on (up to 1.19); single shapes scatter by 6 %
-    // to either side below 8 tiles.  256 nodes x 4 heads on one KV head at
+    // of 2 tiles, 1.01 to 1.03 at 3 to 6, 1.00 at 7, 1.02 at 8, 1.01 to 1.04 at
+    // 10 to 13 and 1.05 from 20 on (up to 1.19); below that single shapes
+    // scatter by 6 % to either side.  256 nodes x 4 heads on one KV head at
     // prefix 40000: 39.6 -> 32.7 us per call.
     a.rows_first = n_kv_heads < 8 && p.tps >= 8;
     const auto inverse = [](int n) { return n > 1 ? (uint32_t)(((1ull << 32) + n - 1) / n) : 0u; };
