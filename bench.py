@@ -304,7 +304,8 @@ TRAFFIC_ENTRIES = {
 MODEL_PROJECTION_KERNELS = {"linear_bf16_kernel": 4, "linear_add_rmsnorm_kernel": 2,
                             "linear_qk_norm_rope_kernel": 1, "linear_reduce_kernel": 1}
 MODEL_PROJECTION_SOURCES = ("paper_2608_00814_amd/csrc/linear.hip", "paper_2608_00814_amd/csrc/stream_core.h",
-                            "paper_2608_00814_amd/csrc/rope.h", "paper_2608_00814_amd/csrc/device_common.h")
+                            "paper_2608_00814_amd/csrc/rope.h", "paper_2608_00814_amd/csrc/runs.h",
+                            "paper_2608_00814_amd/csrc/device_common.h")
 CALIBRATION_KERNEL = "CUDAFunctorOnSelf_add<float>"  # torch.add(src, 1.0, out=dst) of --calibrate-copy-mib
 
 

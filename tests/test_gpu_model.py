@@ -212,6 +212,35 @@ def test_linear_add_rmsnorm(N, K, O):
     assert gh.row_rel_err(_host_f64(out), om.rmsnorm(h_fused.double().cpu().numpy(), f64(nw), 1e-6)) <= TOL
 
 
+@pytest.mark.parametrize("N,K,O", [
+    (256, 8256, 100),   # one tile: as many runs as chunks
+    (256, 8256, 200),   # two runs of two chunks among 256
+    (130, 16448, 640),  # five longer runs
+    (256, 9216, 1000),  # every other run longer
+    (100, 27648, 512),  # runs of 6 and 7 chunks under a long K
+])
+@pytest.mark.parametrize("packed", [True, False], ids=["packed", "rows"])
+def test_linear_spread_runs(N, K, O, packed):
+    """More than 4 MiB of x: the longer stream-K runs are dealt evenly."""
+    print(f"case linear spread runs N={N} K={K} O={O} packed={packed}", flush=True)
+    rs = np.random.default_rng(N + K + O)
+    x, w = _bits(rs, (N, K)), _bits(rs, (O, K), 0.02)
+    xd, wd = _dev_bf16(x), _dev_bf16(w)
+    wl_ = ooo.linear_pack(wd) if packed else wd
+    ref = f64(x) @ f64(w).T
+    ws = torch.full((ooo.linear_workspace(N, K, O),), 0xFF, dtype=torch.uint8, device=DEV)
+    y = torch.full((N, O), float("nan"), dtype=torch.float32, device=DEV)
+    ooo.linear(xd, wl_, y, ooo.EPI_STORE_F32, ws)
+    assert gh.row_rel_err(y.double().cpu().numpy(), ref) <= F32_OUT_TOL
+    if O > 600:  # the fused epilogue (its refusal of very few tiles is the contract's)
+        h = torch.zeros(N, O, dtype=torch.float32, device=DEV)
+        out = torch.empty(N, O, dtype=torch.bfloat16, device=DEV)
+        ones = torch.ones(O, dtype=torch.bfloat16, device=DEV)
+        ooo.linear_add_rmsnorm(xd, wl_, h, ones, 1e-6, out, ws)
+        assert torch.equal(h, y)
+        assert gh.row_rel_err(_host_f64(out), om.rmsnorm(h.double().cpu().numpy(), np.ones(O), 1e-6)) <= TOL
+
+
 @pytest.mark.parametrize("N,Hq,Hkv,D,P,bound", [(64, 32, 8, 128, 4096, None), (33, 4, 2, 64, 100, None),
                                                 (1, 8, 2, 128, 0, None), (20, 16, 8, 128, 700, 2000)])
 def test_linear_qk_norm_rope(N, Hq, Hkv, D, P, bound):
