@@ -299,10 +299,14 @@ TRAFFIC_ENTRIES = {
 }
 # The projection kernels of one fused decoder layer (ModelRunner.forward):
 # four streaming products (qkv, o, gate+up, down), then the qkv epilogue
-# (norms, rotation, cache writes), two residual-add + RMSNorm epilogues and
-# the SwiGLU reduce.  Count per layer, and the sources they are built from.
+# (norms, rotation, cache writes), two residual-add + RMSNorm epilogues and,
+# where gate+up goes through partial sums, the SwiGLU reduce; by whole columns
+# it is one kernel of its own.  Count per layer, and the sources they are built
+# from.
 MODEL_PROJECTION_KERNELS = {"linear_bf16_kernel": 4, "linear_add_rmsnorm_kernel": 2,
                             "linear_qk_norm_rope_kernel": 1, "linear_reduce_kernel": 1}
+MODEL_PROJECTION_KERNELS_COLUMNS = {"linear_bf16_kernel": 3, "linear_swiglu_kernel": 1,
+                                    "linear_add_rmsnorm_kernel": 2, "linear_qk_norm_rope_kernel": 1}
 MODEL_PROJECTION_SOURCES = ("paper_2608_00814_amd/csrc/linear.hip", "paper_2608_00814_amd/csrc/stream_core.h",
                             "paper_2608_00814_amd/csrc/rope.h", "paper_2608_00814_amd/csrc/runs.h",
                             "paper_2608_00814_amd/csrc/device_common.h")
@@ -356,7 +360,8 @@ def traffic_record(workload: str, fetch_csv: str, write_csv: str, calibrate_mib:
     if workload in mw.MODEL_CONFIGS:
         n_layers = mw.MODEL_CONFIGS[workload].n_layers
         kernels = {}
-        for part, per_layer in MODEL_PROJECTION_KERNELS.items():
+        columns = any("linear_swiglu_kernel" in k for k in fetch)
+        for part, per_layer in (MODEL_PROJECTION_KERNELS_COLUMNS if columns else MODEL_PROJECTION_KERNELS).items():
             ks = [k for k in fetch if part in k]
             if len(ks) != 1:
                 raise ValueError(f"expected one instantiation of {part} in the profile, found {ks}")

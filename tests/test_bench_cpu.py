@@ -165,6 +165,23 @@ def test_traffic_record_of_the_model_projections(tmp_path):
     assert set(e["sources"]) == set(bench.MODEL_PROJECTION_SOURCES)
 
 
+def test_traffic_record_of_a_gate_up_projection_by_whole_columns(tmp_path):
+    """A profile in which gate+up is one kernel of its own has three
+    stream-K products a layer and no SwiGLU reduce."""
+    from paper_2608_00814_amd import model_workload as mw
+    cal = "void at::native::vectorized_elementwise_kernel<4, at::native::CUDAFunctorOnSelf_add<float>, int>(int)"
+    kib = {"linear_bf16_kernel<2, true>": (40.0, 4.0), "linear_swiglu_kernel<2, 1, true>": (70.0, 6.0),
+           "linear_add_rmsnorm_kernel": (3.0, 2.0), "linear_qk_norm_rope_kernel<128>": (2.0, 1.0)}
+    f, w = tmp_path / "fetch.csv", tmp_path / "write.csv"
+    name = "void ooo::(anonymous namespace)::{}(int)".format
+    _counter_csv(f, "FETCH_SIZE", [(cal, 1024.0)] + [(name(k), v[0]) for k, v in kib.items()])
+    _counter_csv(w, "WRITE_SIZE", [(cal, 1024.0)] + [(name(k), v[1]) for k, v in kib.items()])
+    e = bench.traffic_record("small-model", str(f), str(w), calibrate_mib=1)["projections"]
+    L = mw.MODEL_CONFIGS["small-model"].n_layers
+    assert e["bytes_per_launch"] == L * 1024 * (3 * 44 + 76 + 2 * 5 + 3)
+    assert e["kernels"]["ooo::linear_swiglu_kernel<2, 1, true>"] == [70.0, 6.0, L]
+
+
 def test_kernel_record_at_the_other_workloads():
     """The other workloads' kernel figures use the headline's byte and flop
     counts: an HBM-bound shape is graded against 8 TB/s, an MFMA-bound one
