@@ -1193,8 +1193,10 @@ Plan make_plan(int N, int Hq, int Hkv, int D, int P, ooo_dtype dt, int force_spl
   // Scratch.  A plan that splits never has more blocks than CUs, nor more
   // splits than 64 or than there are tiles; the query counts the blocks of a
   // KV head that these bounds allow, which no smaller trie and no shorter
-  // prefix exceeds, so one workspace serves them all.  A forced split count
-  // asks for exactly its own partials.
+  // prefix exceeds, so one workspace serves them all.  A call asks for the same
+  // bytes, also where its own plan has fewer splits: a workspace that a later
+  // call of the request would find too small is refused at the first.  A
+  // forced split count asks for exactly its own partials.
   long long blocks = (long long)p.splits * p.row_blocks;
   bool wanted = p.splits > 1;
   if (force_splits <= 0) {
